@@ -67,7 +67,8 @@ HBM_PEAK_GBS = 8000.0         # MI355X HBM3E peak
 FP32_VECTOR_PEAK_TFS = 157.3  # MI355X fp32 vector peak (packed FMA)
 TRAFFIC_BASE = os.path.join(ROOT, "profiles", "traffic_spmm_pipe_512x512_14x14_b256")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1911_09723_amd", "csrc", f)
-                  for f in ("spmm_kernels.hip", "spmm_indexed.hip", "spmm_outer.hip", "planner.cpp", "planner.hpp")]
+                  for f in ("spmm_kernels.hip", "spmm_indexed.hip", "spmm_outer.hip", "spmm_half.hip",
+                            "planner.cpp", "planner.hpp")]
 COPY_BYTES = 256 << 20        # calibration copy: 256 MiB read + 256 MiB written
 CALIBRATION_KERNEL = "neg_kernel"  # torch.neg(a, out=b): a plain elementwise copy
 METRIC = "effective GFLOP/s (2*nnz*HW*N) + HBM GB/s % peak, sparse 1x1 conv"
@@ -415,14 +416,17 @@ def summarize(layer, r, dw=False):
         "plan": {k: r["info"][k] for k in ("kernel", "group_lanes", "tile_cols", "waves", "lds_bytes", "slots",
                                            "max_parts", "indexed_min_cols")},
     }
-    # the kernel the runs took, as spconv_run chooses it: outer-product, then
+    # the kernel the runs took, as spconv_run chooses it: the half kernel (fp16
+    # layers up to its widest input), outer-product, then
     # register-indexed (forced, or automatic for this many columns), else the
     # plan's LDS-strip or direct-load kernel
     cols = layer.n * layer.hw
     imc = r["info"]["indexed_min_cols"]
     omc = r["info"]["outer_min_cols"]
     forced = r.get("forced_kernel")
-    if forced == 4 or (forced in (None, 0) and omc > 0 and cols >= omc):
+    if forced in (None, 0) and layer.storage == "f16" and layer.cin <= 1216 and not r["info"]["dw_stride"]:
+        run = "half"
+    elif forced == 4 or (forced in (None, 0) and omc > 0 and cols >= omc):
         run = "outer"
     elif forced == 3 or (forced in (None, 0) and imc > 0 and cols >= imc):
         run = "indexed"
@@ -487,8 +491,8 @@ def _read_counter_dir(d, counter):
 
 
 def _layer_kernel(name):
-    """A kernel of the sparse 1x1 (strip, direct, register-indexed or outer-product)."""
-    return "spmm" in name or "outer_kernel" in name
+    """A kernel of the sparse 1x1 (strip, direct, register-indexed, outer-product or half)."""
+    return "spmm" in name or "outer_kernel" in name or "half_kernel" in name
 
 
 def traffic_summary(fetch_dir, write_dir, commands, out_base):

@@ -73,6 +73,12 @@ struct DevicePlan {
     const int32_t *owave_ptr = nullptr;
     const int32_t *owave_oct = nullptr;
     int64_t outer_min_cols = 0;         // automatic choice: runs of at least this many columns take it (0: never)
+    // half kernel (planner.hpp); hkb = 0: the plan has none
+    int32_t hkb = 0;
+    const uint16_t *hfrag = nullptr;
+    const float *tbias = nullptr;
+    const int32_t *trow_ptr = nullptr;
+    const uint32_t *tent = nullptr;
     // a pass over one channel range of a wider input (spconv_api.cpp): X's
     // channels per image (0: cin), and whether the pass adds to the partial
     // sums already in Y (every pass but the first)
@@ -111,6 +117,13 @@ int32_t outer_lds_bytes(const DevicePlan &p);
 // 4 and 16-byte aligned x and y (whole 4-column vectors per image).
 hipError_t launch_outer(const DevicePlan &p, const void *x, void *y, int32_t m, int32_t hw, int32_t vec,
                         int64_t x_bytes, hipStream_t stream);
+
+// Once per plan: allow the half kernel its LDS.
+hipError_t prepare_half(const DevicePlan &p);
+// One launch of the half kernel over all m = N * hw columns (fp16 x and y).
+// `vec` != 0 promises hw a multiple of 4 and 8-byte aligned x and y.
+hipError_t launch_half(const DevicePlan &p, const void *x, void *y, int32_t m, int32_t hw, int32_t vec,
+                       int64_t x_bytes, int64_t y_bytes, hipStream_t stream);
 
 // Once per plan, on its device: raise the kernel's dynamic-LDS limit when
 // needed and record num_cus and blocks_per_cu.

@@ -23,11 +23,8 @@ uint16_t float_to_half_rne(float v) {
         return static_cast<uint16_t>(sign | 0x7c00u);
     if (a >= 0x38800000u) {  // normal half range, |v| >= 2^-14
         const uint32_t m = a - 0x38000000u;  // exponent bias 127 -> 15
-        uint32_t r = m >> 13;
-        const uint32_t rem = m & 0x1fffu;
-        if (rem > 0x1000u || (rem == 0x1000u && (r & 1u)))
-            ++r;  // a mantissa carry correctly bumps the exponent
-        return static_cast<uint16_t>(sign | r);
+        // ties to even; a mantissa carry correctly bumps the exponent
+        return static_cast<uint16_t>(sign | ((m + 0xfffu + ((m >> 13) & 1u)) >> 13));
     }
     if (a < 0x33000000u)  // below 2^-25: rounds to zero (2^-25 itself ties to even zero)
         return static_cast<uint16_t>(sign);
@@ -44,17 +41,21 @@ uint16_t float_to_half_rne(float v) {
 }
 
 float half_to_float(uint16_t h) {
-    const int sign = (h >> 15) & 1;
-    const int expo = (h >> 10) & 0x1f;
-    const int frac = h & 0x3ff;
+    const uint32_t sign = static_cast<uint32_t>(h & 0x8000) << 16;
+    const uint32_t expo = (h >> 10) & 0x1f, frac = h & 0x3ff;
+    uint32_t f;
+    if (expo == 0) {  // zero or subnormal: frac units of 2^-24, exact in fp32
+        const float v = static_cast<float>(frac) * 0x1p-24f;
+        std::memcpy(&f, &v, 4);
+    } else if (expo == 31) {
+        f = frac ? 0x7fc00000u : 0x7f800000u;
+    } else {
+        f = (expo + 112) << 23 | frac << 13;
+    }
+    f |= sign;
     float v;
-    if (expo == 0)
-        v = std::ldexp(static_cast<float>(frac), -24);
-    else if (expo == 31)
-        v = frac ? NAN : INFINITY;
-    else
-        v = std::ldexp(static_cast<float>(frac | 0x400), expo - 25);
-    return sign ? -v : v;
+    std::memcpy(&v, &f, 4);
+    return v;
 }
 
 Status validate(const Input &in, std::string &err) {
@@ -699,6 +700,8 @@ Status build_plan(const Input &in_arg, const Options &opt, PackedPlan &p, std::s
         p.rlane_cols = opt.lane_cols;
     }
     p.auto_kernel = opt.kernel == 0;
+    if (p.auto_kernel)
+        build_half(in, p);
     if (outer_supported(in) && (opt.kernel == 0 || opt.kernel == 4)) {
         build_outer(in, p);
         p.use_outer = opt.kernel == 4;
@@ -1414,6 +1417,36 @@ bool outer_supported(const Input &in) {
            (in.block_rows == 1 && in.storage == 0 && in.cin <= kOuterMaxCin16);
 }
 
+void build_half(const Input &in, PackedPlan &p) {
+    const int64_t kb = (in.cin + 31) / 32, tiles = (static_cast<int64_t>(in.cout) + 31) / 32 * 2;
+    if (in.storage != 1 || in.dw_stride || in.cin > kHalfMaxCin || tiles * kb * 1024 > kHalfMaxFragBytes)
+        return;
+    p.hkb = static_cast<int32_t>(kb);
+    const int32_t k = in.block_rows, rows = in.cout / k;
+    p.tbias.assign(static_cast<size_t>(tiles) * 16, 0.0f);
+    if (in.bias)
+        std::copy(in.bias, in.bias + in.cout, p.tbias.begin());
+    p.trow_ptr.resize(static_cast<size_t>(in.cout) + 1);
+    p.trow_ptr[0] = 0;
+    for (int32_t r = 0; r < in.cout; ++r)
+        p.trow_ptr[r + 1] = p.trow_ptr[r] + in.row_ptr[r / k + 1] - in.row_ptr[r / k];
+    p.tent.resize(static_cast<size_t>(p.trow_ptr[in.cout]) * 2);
+    p.hfrag.assign(static_cast<size_t>(tiles * kb * 512), 0);
+    for (int32_t b = 0; b < rows; ++b)
+        for (int32_t t = in.row_ptr[b]; t < in.row_ptr[b + 1]; ++t) {
+            const int32_t c = in.col_idx[t], at = t - in.row_ptr[b];
+            for (int32_t i = 0; i < k; ++i) {
+                const int32_t r = b * k + i;
+                const uint16_t h = float_to_half_rne(in.values[static_cast<int64_t>(t) * k + i]);
+                const float v = half_to_float(h);
+                uint32_t *e = &p.tent[2 * (static_cast<size_t>(p.trow_ptr[r]) + at)];
+                e[0] = static_cast<uint32_t>(c);
+                std::memcpy(&e[1], &v, 4);
+                p.hfrag[static_cast<size_t>(((r / 16) * kb + c / 32) * 512 + (r % 16 + 16 * (c % 32 / 8)) * 8 + c % 8)] = h;
+            }
+        }
+}
+
 void build_outer(const Input &in, PackedPlan &p) {
     const int32_t k = in.block_rows;
     const int32_t rows = in.cout / k;
@@ -1433,8 +1466,6 @@ void build_outer(const Input &in, PackedPlan &p) {
     p.oocts = O;
     p.ozrow = (in.cin + per_copy - 1) / per_copy * per_copy;
     const uint32_t zoff = static_cast<uint32_t>(p.ozrow * row_bytes);
-    p.orec.clear();
-    p.ooff.clear();
     p.ooct_tab.assign(static_cast<size_t>(O) * kOctWords, 0);
     std::vector<int64_t> steps(O);
     int32_t quads = 0;
@@ -1450,34 +1481,27 @@ void build_outer(const Input &in, PackedPlan &p) {
         quads += nq;
         for (int32_t g = 0; g < G; ++g)
             tab[2 + g] = o * G + g < rows ? order[o * G + g] : -1;
-        for (int32_t j = 0; j < nq; ++j) {
-            for (int32_t u = 0; u < slots; ++u) {
-                const int32_t g = u / kw, t = u % kw, rb = tab[2 + g];
-                for (int32_t h = 0; h < kOuterQuadSteps; ++h) {
-                    const int32_t s = kOuterQuadSteps * j + h;
-                    uint32_t w = 0;
-                    if (rb >= 0 && s < len(rb)) {
-                        float v = in.values[(static_cast<int64_t>(in.row_ptr[rb]) + s) * k + t];
-                        if (in.storage == 1)
-                            v = half_to_float(float_to_half_rne(v));
-                        std::memcpy(&w, &v, 4);
-                    }
-                    p.orec.push_back(w);
-                }
-            }
-            for (int32_t g = 0; g < G; ++g) {
-                const int32_t rb = tab[2 + g];
-                for (int32_t h = 0; h < kOuterQuadSteps; ++h) {
-                    const int32_t s = kOuterQuadSteps * j + h;
-                    p.ooff.push_back(rb >= 0 && s < len(rb)
-                                         ? static_cast<uint32_t>(in.col_idx[in.row_ptr[rb] + s] * row_bytes)
-                                         : zoff);
+    }
+    // padding everywhere, then the stored blocks
+    p.orec.assign(static_cast<size_t>(quads + kOuterAhead) * slots * 4, 0u);
+    p.ooff.assign(static_cast<size_t>(quads + kOuterAhead) * G * 4, zoff);
+    for (int32_t o = 0; o < O; ++o) {
+        const int32_t *tab = &p.ooct_tab[static_cast<size_t>(o) * kOctWords];
+        for (int32_t g = 0; g < G; ++g) {
+            const int32_t rb = tab[2 + g];
+            for (int32_t s = 0; rb >= 0 && s < len(rb); ++s) {
+                const int64_t t = in.row_ptr[rb] + s, quad = tab[0] + s / kOuterQuadSteps;
+                const int32_t h = s % kOuterQuadSteps;
+                p.ooff[static_cast<size_t>((quad * G + g) * 4 + h)] = static_cast<uint32_t>(in.col_idx[t] * row_bytes);
+                for (int32_t i = 0; i < kw; ++i) {
+                    float v = in.values[t * k + i];
+                    if (in.storage == 1)
+                        v = half_to_float(float_to_half_rne(v));
+                    std::memcpy(&p.orec[static_cast<size_t>((quad * slots + g * kw + i) * 4 + h)], &v, 4);
                 }
             }
         }
     }
-    p.orec.insert(p.orec.end(), static_cast<size_t>(kOuterAhead) * slots * 4, 0u);
-    p.ooff.insert(p.ooff.end(), static_cast<size_t>(kOuterAhead) * G * 4, zoff);
 
     // wave lists: even tiles, then odd tiles continuing from the even loads
     const int32_t W = std::min<int32_t>(kMaxWaves, O);

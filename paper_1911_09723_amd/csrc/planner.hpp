@@ -215,6 +215,18 @@ constexpr int32_t kOuterQuadSteps = 4;
 constexpr int32_t kOuterMaxCin32 = 632;
 constexpr int32_t kOuterMaxCin16 = 1264;
 
+// Half kernel (fp16 storage, the automatic choice): W as dense fragments of
+// the matrix cores' fp16 16x16x32 instruction.  Tile t covers output channels
+// 16 t .. 16 t + 15 (an even number of tiles, rows past cout zero), block b
+// input channels 32 b .. 32 b + 31 (past cin zero); fragment (t, b) starts at
+// half 512 (t * hkb + b), and its lane l holds the 8 weights of row 16 t + l %
+// 16 at channels 32 b + 8 (l / 16) .. + 7.  Beside them the stored weights by
+// output channel (trow_ptr, tent: channel, fp32 bits), which the kernel sums
+// instead wherever it meets an infinity or a NaN, and the biases (tbias,
+// padded to whole groups of 32 rows).
+constexpr int32_t kHalfMaxCin = 1216;               // 64 columns of X and their table fit in LDS
+constexpr int64_t kHalfMaxFragBytes = 16 << 20;     // dense weights kept beside the packed ones
+
 struct Input {
     int32_t cout = 0, cin = 0, block_rows = 1;
     // input channels per block (Fig. 5: 4x1 and 2x2 blocks beside 1x4): block t
@@ -330,6 +342,12 @@ struct PackedPlan {
     std::vector<int32_t> ooct_tab;
     std::vector<int32_t> owave_ptr;
     std::vector<int32_t> owave_oct;
+    // half kernel (planner.hpp, "Half kernel"); hkb = 0 when the plan has none
+    int32_t hkb = 0;                 // blocks of 32 input channels
+    std::vector<uint16_t> hfrag;
+    std::vector<float> tbias;
+    std::vector<int32_t> trow_ptr;
+    std::vector<uint32_t> tent;
     std::vector<int32_t> perm;     // block rows in processing order
     std::vector<int32_t> row_nnz;  // stored blocks per block row (host only; for unpacking)
     // statistics
@@ -398,6 +416,9 @@ void build_indexed(const Input &in, const std::vector<int32_t> &order, PackedPla
 bool outer_supported(const Input &in);
 // Build its group sets, records and wave lists (fields o* of PackedPlan).
 void build_outer(const Input &in, PackedPlan &p);
+// Build the half kernel's fragments (fields h*, t* of PackedPlan), when the
+// layer is in its range (fp16 storage, cin <= kHalfMaxCin, no depthwise stage).
+void build_half(const Input &in, PackedPlan &p);
 // Rebuild block-CSR arrays from the lockstep kernel's records, checking their
 // structure (lockstep padding, ascending channels, offsets, wave lists).
 // E_FORMAT with `err` set when inconsistent or absent.

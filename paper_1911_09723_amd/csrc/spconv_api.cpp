@@ -108,7 +108,7 @@ spconv_status upload(spconv_plan_s *pl, bool use_static) {
         const void *src;
         size_t bytes;
         size_t off;
-    } parts[26] = {
+    } parts[30] = {
         {h.idx.data(), h.idx.size() * sizeof(int32_t), 0},
         {h.val.data(), h.val.size() * sizeof(float), 0},
         {h.hdr.data(), h.hdr.size() * sizeof(int32_t), 0},
@@ -135,11 +135,28 @@ spconv_status upload(spconv_plan_s *pl, bool use_static) {
         {h.owave_ptr.data(), h.owave_ptr.size() * sizeof(int32_t), 0},
         {h.owave_oct.data(), h.owave_oct.size() * sizeof(int32_t), 0},
         {h.ooff.data(), h.ooff.size() * sizeof(uint32_t), 0},
+        {h.hfrag.data(), h.hfrag.size() * sizeof(uint16_t), 0},
+        {h.tbias.data(), h.tbias.size() * sizeof(float), 0},
+        {h.trow_ptr.data(), h.trow_ptr.size() * sizeof(int32_t), 0},
+        {h.tent.data(), h.tent.size() * sizeof(uint32_t), 0},
     };
+    constexpr int kDenseParts = 26;  // parts from here on: the half kernel's
     size_t total = 0;
-    for (Part &p : parts) {
-        p.off = total;
-        total = align_up(total + std::max<size_t>(p.bytes, 16), 256);
+    auto layout = [&]() {
+        total = 0;
+        for (Part &p : parts) {
+            p.off = total;
+            total = align_up(total + std::max<size_t>(p.bytes, 16), 256);
+        }
+    };
+    layout();
+    if (use_static && total > kStaticPlanBytes && pl->dev.hkb) {
+        // without its dense weights the image may fit: the plan then runs the
+        // other kernels
+        pl->dev.hkb = 0;
+        for (int i = kDenseParts; i < 30; ++i)
+            parts[i].bytes = 0;
+        layout();
     }
     if (use_static && total > kStaticPlanBytes)  // before any HIP call
         return fail(SPCONV_E_SHAPE, "the plan's device image needs " + std::to_string(total) +
@@ -214,6 +231,10 @@ spconv_status upload(spconv_plan_s *pl, bool use_static) {
     d.owave_ptr = reinterpret_cast<const int32_t *>(base + parts[23].off);
     d.owave_oct = reinterpret_cast<const int32_t *>(base + parts[24].off);
     d.ooff = reinterpret_cast<const uint32_t *>(base + parts[25].off);
+    d.hfrag = reinterpret_cast<const uint16_t *>(base + parts[26].off);
+    d.tbias = reinterpret_cast<const float *>(base + parts[27].off);
+    d.trow_ptr = reinterpret_cast<const int32_t *>(base + parts[28].off);
+    d.tent = reinterpret_cast<const uint32_t *>(base + parts[29].off);
     return SPCONV_OK;
 }
 
@@ -293,6 +314,7 @@ void fill_device_geometry(spconv_plan_s *pl) {
     d.owaves = h.owaves;
     d.ozrow = h.ozrow;
     d.ooff_bytes = static_cast<int32_t>(h.ooff.size() * sizeof(uint32_t));
+    d.hkb = h.hkb;
 }
 
 bool ranges_overlap(const void *a, size_t abytes, const void *b, size_t bbytes) {
@@ -391,6 +413,8 @@ spconv_status create_plan(spconv_plan *out, const spconv::Input &in, const spcon
                 pe = spconv::prepare_indexed(pl->dev);
             if (pe == hipSuccess && pl->dev.oocts > 0)
                 pe = spconv::prepare_outer(pl->dev);
+            if (pe == hipSuccess && pl->dev.hkb > 0)
+                pe = spconv::prepare_half(pl->dev);
             pl->dev.indexed_min_cols = indexed_min_cols(pl->host, pl->dev);
             pl->dev.outer_min_cols = outer_min_cols(pl->host, pl->dev);
             if (pe != hipSuccess)
@@ -689,12 +713,13 @@ spconv_status spconv_run(spconv_plan plan, const void *x, void *y, int32_t n, in
     // the kernels address X and Y relative to the first image of a tile with
     // 32-bit byte offsets: the images one tile's columns touch (at most
     // (tile_cols - 1) / hw + 2 of them) must span less than 2^31 bytes of each
+    const int64_t image_bytes = std::max(ihw * p.cin, hw * p.cout) * static_cast<int64_t>(e);
+    auto fits = [&](int64_t cols) { return ((cols - 1) / hw + 2) * image_bytes < (int64_t(1) << 31) - 16; };
     const bool outer = p.use_outer || (plan->dev.outer_min_cols > 0 && m >= plan->dev.outer_min_cols);
     const bool indexed = !outer && (plan->dev.use_indexed ||
                                     (plan->dev.indexed_min_cols > 0 && m >= plan->dev.indexed_min_cols));
     const int64_t tile_cols = outer ? p.otw : indexed ? 64 * 6 : p.tile_cols;
-    const int64_t span = (tile_cols - 1) / hw + 2;
-    if (span * std::max(ihw * p.cin, hw * p.cout) * static_cast<int64_t>(e) >= (int64_t(1) << 31) - 16)
+    if (!fits(tile_cols))
         return fail(SPCONV_E_UNSUPPORTED,
                     "h * w * channels too large: the images of one tile must span less than 2^31 bytes");
     if (plan->host_only)
@@ -724,7 +749,13 @@ spconv_status spconv_run(spconv_plan plan, const void *x, void *y, int32_t n, in
                                      xel * static_cast<int64_t>(e) - skip, yel * static_cast<int64_t>(e), h, w,
                                      static_cast<int32_t>(ow), static_cast<hipStream_t>(stream));
         }
-    } else if (outer)
+    } else if (plan->dev.hkb > 0)
+        he = spconv::launch_half(plan->dev, x, y, static_cast<int32_t>(m), static_cast<int32_t>(hw),
+                                 hw % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 8 == 0 &&
+                                     reinterpret_cast<uintptr_t>(y) % 8 == 0,
+                                 xel * static_cast<int64_t>(e), yel * static_cast<int64_t>(e),
+                                 static_cast<hipStream_t>(stream));
+    else if (outer)
         he = spconv::launch_outer(plan->dev, x, y, static_cast<int32_t>(m), static_cast<int32_t>(hw),
                                   hw % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
                                       reinterpret_cast<uintptr_t>(y) % 16 == 0,

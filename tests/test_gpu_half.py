@@ -1,0 +1,104 @@
+"""GPU parity of the half kernel (fp16 storage, the automatic choice): dense
+fragments of W on the matrix cores.
+
+Each case is compared with the oracle to the fp16 tolerance.  The sizes sit at
+the kernel's edges: input channels around blocks of 32 and 8, output channels
+around groups of 32, 16 and 4 rows, column counts around tiles of 64 and 128
+(64-column tiles where a run has few or the input is wide), planes whose
+4-column units lie in one image, straddle two (H*W not a multiple of 4) or
+more (H*W below 4), and the widest input of its range and one past it.
+"""
+
+import zlib
+
+import numpy as np
+import pytest
+
+from synth import make_layer, densify
+from gpu_util import gpu_run, assert_parity, note, to_gpu, device
+
+pytestmark = pytest.mark.gpu
+
+# (cin, cout, h, w, n, sparsity, k, act)
+SHAPES = [
+    (32, 32, 8, 8, 1, 0.5, 1, "relu"),        # one tile of 64 columns, one block, one row group
+    (33, 36, 8, 8, 1, 0.8, 4, "none"),        # a block with one channel, a group with 4 rows
+    (31, 30, 4, 15, 1, 0.8, 2, "relu6"),      # ragged block, group and tile
+    (7, 4, 1, 4, 1, 0.0, 4, "none"),          # the smallest vector case
+    (9, 1, 1, 1, 1, 0.0, 1, "relu"),          # one column
+    (40, 65, 1, 3, 7, 0.7, 1, "relu"),        # H*W below 4: element loads and stores
+    (72, 100, 1, 2, 45, 0.8, 4, "none"),
+    (24, 40, 1, 1, 130, 0.5, 1, "relu6"),     # units of 4 images
+    (48, 33, 5, 5, 6, 0.8, 1, "relu"),        # 150 columns: straddling units, a ragged last unit
+    (64, 48, 3, 3, 29, 0.8, 2, "none"),       # 261 columns, H*W = 9
+    (320, 128, 7, 7, 700, 0.9, 4, "relu6"),   # 128-column tiles, odd planes, the widest at that tile
+    (321, 128, 14, 14, 90, 0.9, 1, "relu"),   # 64-column tiles
+    (128, 672, 14, 14, 96, 0.9, 4, "relu6"),  # 128-column tiles, row groups over several workgroups
+    (1216, 40, 7, 7, 3, 0.9, 1, "relu"),      # the widest input
+    (1217, 40, 7, 7, 3, 0.9, 1, "relu"),      # past it
+]
+
+
+@pytest.mark.parametrize("spec", SHAPES, ids=lambda s: "%d-%d-%dx%d-n%d-s%g-k%d-%s" % s)
+def test_half_matches_oracle(spec):
+    cin, cout, h, w, n, s, k, act = spec
+    layer = make_layer(cin, cout, h, w, n, s, block_rows=k, storage="f16", act=act,
+                       seed=zlib.crc32(repr(spec).encode()) % 1000)
+    note("half %s" % (spec,))
+    assert_parity(layer, gpu_run(layer), what=str(spec))
+
+
+@pytest.mark.parametrize("hw", [(8, 8), (7, 7), (1, 2)])
+def test_half_alignment_and_batch_do_not_change_bits(hw):
+    """x and y one and two elements off an 8-byte boundary, and each image on
+    its own: the same bits (the order of summation is the plan's)."""
+    import torch
+    from paper_1911_09723_amd import Plan
+    layer = make_layer(72, 100, hw[0], hw[1], 5, 0.8, storage="f16", act="none", seed=3)
+    note("half unaligned %s" % (hw,))
+    ref = gpu_run(layer)
+    parts = [gpu_run(layer, x=layer.x[i:i + 1]) for i in range(5)]
+    assert np.array_equal(ref.view(np.uint16), np.concatenate(parts).view(np.uint16))
+    plan = Plan.from_layer(layer)
+    try:
+        for off in (1, 2):
+            flat = to_gpu(np.concatenate([np.zeros(off, np.float16), layer.x.ravel()]))
+            ybuf = torch.full((off + ref.size + 8,), 7.0, dtype=torch.float16, device=device())
+            y = ybuf[off:off + ref.size].view(ref.shape)
+            plan.run(flat[off:].view(layer.x.shape), y)
+            torch.cuda.synchronize()
+            assert np.array_equal(y.cpu().numpy().view(np.uint16), ref.view(np.uint16))
+            assert torch.all(ybuf[:off] == 7.0) and torch.all(ybuf[off + ref.size:] == 7.0)
+    finally:
+        plan.close()
+
+
+@pytest.mark.parametrize("hw", [(8, 8), (7, 7), (1, 1)])
+@pytest.mark.parametrize("act", ["relu6", "none"])
+def test_half_infinities_and_nans_stay_on_their_rows(hw, act):
+    """Non-finite inputs reach the rows that store a weight at their channel
+    and no other (the dense product alone would spread 0 * inf to all)."""
+    layer = make_layer(70, 45, hw[0], hw[1], 4, 0.8, storage="f16", act=act, seed=17)
+    x = layer.x.copy()
+    x[0, 3, 0, 0] = np.inf
+    x[1, 40, -1, -1] = -np.inf
+    x[3, 69, -1, -1] = np.nan
+    x[3, 12, 0, 0] = np.inf
+    note("half non-finite %s %s" % (hw, act))
+    y = gpu_run(layer, x=x).astype(np.float64)
+    wd = densify(45, 70, 1, layer.row_ptr, layer.col_idx, layer.values)
+    stored = densify(45, 70, 1, layer.row_ptr, layer.col_idx, np.ones_like(layer.values)) > 0
+    finite = np.where(np.isfinite(x), x, 0).astype(np.float64)
+    s = np.einsum("rc,nchw->nrhw", wd, finite) + layer.bias[None, :, None, None]
+    for n, c, i, j in np.argwhere(~np.isfinite(x)):
+        for r in np.flatnonzero(stored[:, c]):
+            s[n, r, i, j] += wd[r, c] * float(x[n, c, i, j])
+    if act == "relu6":
+        s = np.where(np.isnan(s), 0.0, np.clip(s, 0, 6))  # a NaN clamps to the lower bound
+    else:
+        s = np.where(np.isnan(s), -np.inf, s)
+    assert np.array_equal(np.isfinite(y), np.isfinite(s))
+    ok = np.isfinite(s)
+    assert np.array_equal(y[~ok], s[~ok])
+    # 2^-11 of the value (one rounding to fp16) and fp32 sums of at most 70 terms
+    assert np.all(np.abs(y[ok] - s[ok]) <= 2e-3 * np.abs(s[ok]) + 1e-4)
