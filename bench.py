@@ -67,7 +67,7 @@ HBM_PEAK_GBS = 8000.0         # MI355X HBM3E peak
 FP32_VECTOR_PEAK_TFS = 157.3  # MI355X fp32 vector peak (packed FMA)
 TRAFFIC_BASE = os.path.join(ROOT, "profiles", "traffic_spmm_pipe_512x512_14x14_b256")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1911_09723_amd", "csrc", f)
-                  for f in ("spmm_kernels.hip", "spmm_indexed.hip", "spmm_outer.hip", "spmm_half.hip",
+                  for f in ("spmm_kernels.hip", "spmm_indexed.hip", "spmm_outer.hip", "spmm_half.hip", "spmm_rows.hip",
                             "planner.cpp", "planner.hpp")]
 COPY_BYTES = 256 << 20        # calibration copy: 256 MiB read + 256 MiB written
 CALIBRATION_KERNEL = "neg_kernel"  # torch.neg(a, out=b): a plain elementwise copy
@@ -419,7 +419,8 @@ def summarize(layer, r, dw=False):
     # the kernel the runs took, as spconv_run chooses it: the half kernel (fp16
     # layers up to its widest input), outer-product, then
     # register-indexed (forced, or automatic for this many columns), else the
-    # plan's LDS-strip or direct-load kernel
+    # plan's LDS-strip or direct-load kernel; automatic fp32 runs of few columns
+    # or up to 160 input channels may take a row kernel instead
     cols = layer.n * layer.hw
     imc = r["info"]["indexed_min_cols"]
     omc = r["info"]["outer_min_cols"]
@@ -432,6 +433,8 @@ def summarize(layer, r, dw=False):
         run = "indexed"
     else:
         run = "direct" if r["info"]["kernel"] == 1 else "strip"
+        if forced in (None, 0) and layer.storage == "f32" and (layer.cin <= 160 or cols <= 8192):
+            run += " or rows"
     out["plan"]["kernel_run"] = run
     out["plan"]["outer_min_cols"] = omc
     if layer.storage == "f16":
@@ -491,8 +494,8 @@ def _read_counter_dir(d, counter):
 
 
 def _layer_kernel(name):
-    """A kernel of the sparse 1x1 (strip, direct, register-indexed, outer-product or half)."""
-    return "spmm" in name or "outer_kernel" in name or "half_kernel" in name
+    """A kernel of the sparse 1x1 (strip, direct, register-indexed, outer-product, half or rows)."""
+    return any(s in name for s in ("spmm", "outer_kernel", "half_kernel", "rows_kernel"))
 
 
 def traffic_summary(fetch_dir, write_dir, commands, out_base):

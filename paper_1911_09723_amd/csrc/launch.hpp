@@ -79,6 +79,14 @@ struct DevicePlan {
     const float *tbias = nullptr;
     const int32_t *trow_ptr = nullptr;
     const uint32_t *tent = nullptr;
+    // row kernels (planner.hpp); trow_ptr null: the plan has none, glist null:
+    // no streams
+    const uint32_t *gent = nullptr;
+    const uint32_t *gdesc = nullptr;
+    const int32_t *glist = nullptr;
+    int32_t groups = 0;          // of the streams
+    int32_t max_row = 0;         // stored weights of the longest output channel
+    int32_t nnz = 0;             // and of all
     // a pass over one channel range of a wider input (spconv_api.cpp): X's
     // channels per image (0: cin), and whether the pass adds to the partial
     // sums already in Y (every pass but the first)
@@ -124,6 +132,21 @@ hipError_t prepare_half(const DevicePlan &p);
 // `vec` != 0 promises hw a multiple of 4 and 8-byte aligned x and y.
 hipError_t launch_half(const DevicePlan &p, const void *x, void *y, int32_t m, int32_t hw, int32_t vec,
                        int64_t x_bytes, int64_t y_bytes, hipStream_t stream);
+
+// Whether a run of `images` planes of hw columns is faster on the row kernel
+// for few columns, and on the LDS row kernel (image_bytes: the larger of one
+// image of x and of y), than on the plan's other kernels.
+bool rows_pay(const DevicePlan &p, int64_t images, int64_t hw);
+bool strip_rows_pay(const DevicePlan &p, int64_t images, int64_t hw, int64_t image_bytes);
+// One launch of the row kernel for few columns over all m = N * hw columns
+// (fp32 x and y of any alignment; hw >= 4).
+hipError_t launch_rows(const DevicePlan &p, const float *x, float *y, int32_t m, int32_t hw, hipStream_t stream);
+// Once per plan: allow the LDS row kernel its LDS.
+hipError_t prepare_strip_rows(const DevicePlan &p);
+// One launch of the LDS row kernel over all m = N * hw columns (fp32 x and y of
+// any alignment; hw >= 4).
+hipError_t launch_strip_rows(const DevicePlan &p, const float *x, float *y, int32_t m, int32_t hw, int64_t x_bytes,
+                             int64_t y_bytes, hipStream_t stream);
 
 // Once per plan, on its device: raise the kernel's dynamic-LDS limit when
 // needed and record num_cus and blocks_per_cu.

@@ -700,8 +700,11 @@ Status build_plan(const Input &in_arg, const Options &opt, PackedPlan &p, std::s
         p.rlane_cols = opt.lane_cols;
     }
     p.auto_kernel = opt.kernel == 0;
-    if (p.auto_kernel)
+    if (p.auto_kernel) {
         build_half(in, p);
+        if (opt.split)
+            build_rows(in, p);
+    }
     if (outer_supported(in) && (opt.kernel == 0 || opt.kernel == 4)) {
         build_outer(in, p);
         p.use_outer = opt.kernel == 4;
@@ -1151,15 +1154,19 @@ void build_indexed(const Input &in, const std::vector<int32_t> &order, PackedPla
             int32_t c, pos;
             int64_t t;
         };
-        std::vector<Ent> ents;
+        // by channel, then slot position: counted, as rows come in position order
+        std::vector<int32_t> next(static_cast<size_t>(in.cin) + 1, 0);
+        for (int32_t rb : members[s])
+            for (int32_t t = in.row_ptr[rb]; t < in.row_ptr[rb + 1]; ++t)
+                ++next[in.col_idx[t] + 1];
+        for (int32_t c = 0; c < in.cin; ++c)
+            next[c + 1] += next[c];
+        std::vector<Ent> ents(next[in.cin]);
         for (int32_t b = 0; b < static_cast<int32_t>(members[s].size()); ++b) {
             const int32_t rb = members[s][b];
             for (int32_t t = in.row_ptr[rb]; t < in.row_ptr[rb + 1]; ++t)
-                ents.push_back({in.col_idx[t], b, t});
+                ents[next[in.col_idx[t]]++] = {in.col_idx[t], b, t};
         }
-        std::stable_sort(ents.begin(), ents.end(), [](const Ent &a, const Ent &b) {
-            return a.c != b.c ? a.c < b.c : a.pos < b.pos;
-        });
         size_t e = 0;
         for (int32_t q = 0; q < nch; ++q) {
             const size_t chunk_start = p.rrec.size();
@@ -1445,6 +1452,100 @@ void build_half(const Input &in, PackedPlan &p) {
                 p.hfrag[static_cast<size_t>(((r / 16) * kb + c / 32) * 512 + (r % 16 + 16 * (c % 32 / 8)) * 8 + c % 8)] = h;
             }
         }
+}
+
+void build_rows(const Input &in, PackedPlan &p) {
+    if (in.storage != 0 || in.dw_stride)
+        return;
+    const int32_t k = in.block_rows, cout = in.cout;
+    auto begin = [&](int32_t r) { return in.row_ptr[r / k]; };
+    auto len = [&](int32_t r) { return in.row_ptr[r / k + 1] - in.row_ptr[r / k]; };
+    p.tbias.assign(static_cast<size_t>(cout), 0.0f);
+    if (in.bias)
+        std::copy(in.bias, in.bias + cout, p.tbias.begin());
+    p.trow_ptr.resize(static_cast<size_t>(cout) + 1);
+    p.trow_ptr[0] = 0;
+    for (int32_t r = 0; r < cout; ++r)
+        p.trow_ptr[r + 1] = p.trow_ptr[r] + len(r);
+    p.tent.resize(static_cast<size_t>(p.trow_ptr[cout]) * 2);
+    for (int32_t r = 0; r < cout; ++r) {
+        uint32_t *d = p.tent.data() + 2 * static_cast<size_t>(p.trow_ptr[r]);
+        const int32_t n = len(r);
+        const int32_t *col = in.col_idx + begin(r);
+        const float *val = in.values + static_cast<int64_t>(begin(r)) * k + r % k;
+        for (int32_t e = 0; e < n; ++e) {
+            d[2 * e] = static_cast<uint32_t>(col[e]);
+            std::memcpy(&d[2 * e + 1], &val[static_cast<int64_t>(e) * k], 4);
+        }
+    }
+    if (in.cin > kRowMaxCin)
+        return;
+    // rows to lists, then lists to wavefronts (a row costs its groups and its epilogue)
+    auto groups = [&](int32_t r) { return std::max(1, (len(r) + kGroupRecs - 1) / kGroupRecs); };
+    constexpr int32_t kWaves = 8, kPer = kRowLists / kWaves;
+    std::vector<int32_t> order(cout);
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return groups(a) > groups(b); });
+    int64_t load[kRowLists] = {};
+    std::vector<int32_t> rows[kRowLists];
+    std::vector<std::pair<int64_t, int32_t>> heap(kRowLists);  // load and list, the least first
+    for (int32_t l = 0; l < kRowLists; ++l)
+        heap[l] = {0, l};
+    for (int32_t r : order) {
+        std::pop_heap(heap.begin(), heap.end(), std::greater<>());
+        const int32_t l = heap.back().second;
+        rows[l].push_back(r);
+        heap.back().first = load[l] += groups(r) + 1;
+        std::push_heap(heap.begin(), heap.end(), std::greater<>());
+    }
+    int32_t by_load[kRowLists];
+    std::iota(by_load, by_load + kRowLists, 0);
+    std::stable_sort(by_load, by_load + kRowLists, [&](int32_t a, int32_t b) { return load[a] > load[b]; });
+    int64_t wave[kWaves] = {};
+    std::vector<int32_t> of[kWaves];
+    for (int32_t l : by_load) {
+        int32_t best = -1;
+        for (int32_t w = 0; w < kWaves; ++w)
+            if (of[w].size() < static_cast<size_t>(kPer) && (best < 0 || wave[w] < wave[best]))
+                best = w;
+        of[best].push_back(l);
+        wave[best] += load[l];
+    }
+    int64_t total = 0;
+    for (int32_t r = 0; r < cout; ++r)
+        total += groups(r);
+    p.gent.assign(static_cast<size_t>(total + 2) * 2 * kGroupRecs, 0u);
+    p.gdesc.assign((static_cast<size_t>(cout) + 1) * 4, 0u);
+    p.glist.clear();
+    size_t at = 0;   // group
+    size_t row = 0;  // description
+    for (int32_t w = 0; w < kWaves; ++w)
+        for (int32_t l : of[w]) {
+            p.glist.push_back(static_cast<int32_t>(row));
+            p.glist.push_back(static_cast<int32_t>(at));
+            std::sort(rows[l].begin(), rows[l].end());
+            for (int32_t r : rows[l]) {
+                uint32_t *d = &p.gdesc[4 * row++];
+                d[0] = static_cast<uint32_t>(r);
+                d[1] = static_cast<uint32_t>(groups(r));
+                std::memcpy(&d[2], &p.tbias[r], 4);
+                const uint32_t *e = p.tent.data() + 2 * static_cast<size_t>(p.trow_ptr[r]);
+                const int32_t n = len(r), ng = groups(r);
+                uint32_t *g = &p.gent[at * 2 * kGroupRecs];
+                for (int32_t i = 0; i < n; ++i) {
+                    uint32_t *at_i = g + i / kGroupRecs * 2 * kGroupRecs + i % kGroupRecs;
+                    at_i[0] = e[2 * i];
+                    at_i[kGroupRecs] = e[2 * i + 1];
+                }
+                for (int32_t i = n; i < ng * kGroupRecs; ++i)  // padding reads the row of zeros, weights are 0
+                    g[i / kGroupRecs * 2 * kGroupRecs + i % kGroupRecs] = static_cast<uint32_t>(in.cin);
+                at += ng;
+            }
+        }
+    p.glist.push_back(static_cast<int32_t>(row));
+    p.glist.push_back(static_cast<int32_t>(at));
+    for (int32_t i = 0; i < kGroupRecs; ++i)
+        p.gent[at * 2 * kGroupRecs + i] = p.gent[(at + 1) * 2 * kGroupRecs + i] = static_cast<uint32_t>(in.cin);
 }
 
 void build_outer(const Input &in, PackedPlan &p) {

@@ -227,6 +227,23 @@ constexpr int32_t kOuterMaxCin16 = 1264;
 constexpr int32_t kHalfMaxCin = 1216;               // 64 columns of X and their table fit in LDS
 constexpr int64_t kHalfMaxFragBytes = 16 << 20;     // dense weights kept beside the packed ones
 
+// Row kernels (fp32, where the automatic choice takes them): a wavefront sums
+// one output channel at a time over many columns.  trow_ptr, tent and tbias as
+// for the half kernel (the kernel for few columns walks them).  The LDS kernel
+// walks streams of groups of kGroupRecs stored weights: a row's weights in
+// ascending channel, the last group padded with weight 0 at channel cin (a row
+// of zeros in LDS), at least one group.  A group is kGroupRecs channels, then
+// their weights (fp32 bits).  Rows are dealt to kRowLists lists, longest first
+// to the least loaded, and the lists to the wavefronts of a workgroup the same
+// way, kRowLists / 8 each, so that lists w * kRowLists / 8 .. are wavefront
+// w's; inside a list rows ascend.  gdesc holds 4 words per row in list order:
+// output channel, groups, bias (fp32 bits), 0; list l has the rows glist[2 l]
+// .. glist[2 l + 2] of it and starts at group glist[2 l + 1].  The streams end
+// with two padding groups and gdesc with a zero entry (read ahead).
+constexpr int32_t kGroupRecs = 4;
+constexpr int32_t kRowLists = 64;
+constexpr int32_t kRowMaxCin = 160;  // a tile of X fits in LDS, and the next one in registers
+
 struct Input {
     int32_t cout = 0, cin = 0, block_rows = 1;
     // input channels per block (Fig. 5: 4x1 and 2x2 blocks beside 1x4): block t
@@ -348,6 +365,10 @@ struct PackedPlan {
     std::vector<float> tbias;
     std::vector<int32_t> trow_ptr;
     std::vector<uint32_t> tent;
+    // row kernels (planner.hpp, "Row kernels"); empty when the plan has none
+    std::vector<uint32_t> gent;
+    std::vector<uint32_t> gdesc;
+    std::vector<int32_t> glist;
     std::vector<int32_t> perm;     // block rows in processing order
     std::vector<int32_t> row_nnz;  // stored blocks per block row (host only; for unpacking)
     // statistics
@@ -419,6 +440,9 @@ void build_outer(const Input &in, PackedPlan &p);
 // Build the half kernel's fragments (fields h*, t* of PackedPlan), when the
 // layer is in its range (fp16 storage, cin <= kHalfMaxCin, no depthwise stage).
 void build_half(const Input &in, PackedPlan &p);
+// Build the row kernels' arrays (fields t*, g* of PackedPlan), when the layer is
+// in their range (fp32 storage, no depthwise stage; g*: cin <= kRowMaxCin).
+void build_rows(const Input &in, PackedPlan &p);
 // Rebuild block-CSR arrays from the lockstep kernel's records, checking their
 // structure (lockstep padding, ascending channels, offsets, wave lists).
 // E_FORMAT with `err` set when inconsistent or absent.

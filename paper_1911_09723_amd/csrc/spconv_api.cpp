@@ -108,7 +108,7 @@ spconv_status upload(spconv_plan_s *pl, bool use_static) {
         const void *src;
         size_t bytes;
         size_t off;
-    } parts[30] = {
+    } parts[33] = {
         {h.idx.data(), h.idx.size() * sizeof(int32_t), 0},
         {h.val.data(), h.val.size() * sizeof(float), 0},
         {h.hdr.data(), h.hdr.size() * sizeof(int32_t), 0},
@@ -139,8 +139,12 @@ spconv_status upload(spconv_plan_s *pl, bool use_static) {
         {h.tbias.data(), h.tbias.size() * sizeof(float), 0},
         {h.trow_ptr.data(), h.trow_ptr.size() * sizeof(int32_t), 0},
         {h.tent.data(), h.tent.size() * sizeof(uint32_t), 0},
+        {h.gent.data(), h.gent.size() * sizeof(uint32_t), 0},
+        {h.gdesc.data(), h.gdesc.size() * sizeof(uint32_t), 0},
+        {h.glist.data(), h.glist.size() * sizeof(int32_t), 0},
     };
-    constexpr int kDenseParts = 26;  // parts from here on: the half kernel's
+    constexpr int kParts = sizeof(parts) / sizeof(parts[0]);
+    constexpr int kDenseParts = 26;  // parts from here on: the half and the row kernels'
     size_t total = 0;
     auto layout = [&]() {
         total = 0;
@@ -150,11 +154,12 @@ spconv_status upload(spconv_plan_s *pl, bool use_static) {
         }
     };
     layout();
-    if (use_static && total > kStaticPlanBytes && pl->dev.hkb) {
-        // without its dense weights the image may fit: the plan then runs the
-        // other kernels
+    bool dense = !h.trow_ptr.empty();
+    if (use_static && total > kStaticPlanBytes && dense) {
+        // without these the image may fit: the plan then runs the other kernels
+        dense = false;
         pl->dev.hkb = 0;
-        for (int i = kDenseParts; i < 30; ++i)
+        for (int i = kDenseParts; i < kParts; ++i)
             parts[i].bytes = 0;
         layout();
     }
@@ -235,6 +240,13 @@ spconv_status upload(spconv_plan_s *pl, bool use_static) {
     d.tbias = reinterpret_cast<const float *>(base + parts[27].off);
     d.trow_ptr = reinterpret_cast<const int32_t *>(base + parts[28].off);
     d.tent = reinterpret_cast<const uint32_t *>(base + parts[29].off);
+    if (!dense)
+        d.trow_ptr = nullptr;
+    if (dense && !h.glist.empty()) {
+        d.gent = reinterpret_cast<const uint32_t *>(base + parts[30].off);
+        d.gdesc = reinterpret_cast<const uint32_t *>(base + parts[31].off);
+        d.glist = reinterpret_cast<const int32_t *>(base + parts[32].off);
+    }
     return SPCONV_OK;
 }
 
@@ -315,6 +327,11 @@ void fill_device_geometry(spconv_plan_s *pl) {
     d.ozrow = h.ozrow;
     d.ooff_bytes = static_cast<int32_t>(h.ooff.size() * sizeof(uint32_t));
     d.hkb = h.hkb;
+    d.groups = h.glist.empty() ? 0 : h.glist.back();
+    d.max_row = 0;
+    for (size_t r = 0; r + 1 < h.trow_ptr.size(); ++r)
+        d.max_row = std::max(d.max_row, h.trow_ptr[r + 1] - h.trow_ptr[r]);
+    d.nnz = h.trow_ptr.empty() ? 0 : h.trow_ptr.back();
 }
 
 bool ranges_overlap(const void *a, size_t abytes, const void *b, size_t bbytes) {
@@ -415,6 +432,8 @@ spconv_status create_plan(spconv_plan *out, const spconv::Input &in, const spcon
                 pe = spconv::prepare_outer(pl->dev);
             if (pe == hipSuccess && pl->dev.hkb > 0)
                 pe = spconv::prepare_half(pl->dev);
+            if (pe == hipSuccess && pl->dev.glist)
+                pe = spconv::prepare_strip_rows(pl->dev);
             pl->dev.indexed_min_cols = indexed_min_cols(pl->host, pl->dev);
             pl->dev.outer_min_cols = outer_min_cols(pl->host, pl->dev);
             if (pe != hipSuccess)
@@ -740,7 +759,15 @@ spconv_status spconv_run(spconv_plan plan, const void *x, void *y, int32_t n, in
     const int64_t qv = 16 / static_cast<int64_t>(e);  // columns in one 16-byte vector
     const int32_t vec = (hw % qv == 0) && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
                         reinterpret_cast<uintptr_t>(y) % 16 == 0;
-    if (!plan->passes.empty()) {
+    // the automatic choices that depend on the run's size: a wavefront per
+    // output channel for few columns, whole rows over LDS tiles for many
+    const int32_t images = static_cast<int32_t>(m / hw);
+    const bool few = spconv::rows_pay(plan->dev, images, hw);
+    const bool strip_rows = !few && spconv::strip_rows_pay(plan->dev, images, hw, image_bytes);
+    if (few) {
+        he = spconv::launch_rows(plan->dev, static_cast<const float *>(x), static_cast<float *>(y),
+                                 static_cast<int32_t>(m), static_cast<int32_t>(hw), static_cast<hipStream_t>(stream));
+    } else if (!plan->passes.empty()) {
         // channel-range passes in order: pass i reads X from its first channel
         for (size_t i = 0; i < plan->passes.size() && he == hipSuccess; ++i) {
             const int64_t skip = static_cast<int64_t>(plan->pass_c0[i]) * ihw * static_cast<int64_t>(e);
@@ -755,6 +782,11 @@ spconv_status spconv_run(spconv_plan plan, const void *x, void *y, int32_t n, in
                                      reinterpret_cast<uintptr_t>(y) % 8 == 0,
                                  xel * static_cast<int64_t>(e), yel * static_cast<int64_t>(e),
                                  static_cast<hipStream_t>(stream));
+    else if (strip_rows)
+        he = spconv::launch_strip_rows(plan->dev, static_cast<const float *>(x), static_cast<float *>(y),
+                                       static_cast<int32_t>(m), static_cast<int32_t>(hw),
+                                       xel * static_cast<int64_t>(e), yel * static_cast<int64_t>(e),
+                                       static_cast<hipStream_t>(stream));
     else if (outer)
         he = spconv::launch_outer(plan->dev, x, y, static_cast<int32_t>(m), static_cast<int32_t>(hw),
                                   hw % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&

@@ -1,0 +1,139 @@
+"""GPU parity of the row kernels (fp32, the automatic choice: one for runs of
+few columns, one over LDS tiles for longer runs of up to 160 input channels).
+
+Each case is compared with the oracle to the fp32 tolerance and bit for bit
+with the direct-load kernel (kernel option 2): both sum each output in
+ascending input channel from zero.  The sizes sit at the kernels' edges: rows
+of no weight and around batches of 8 and groups of 4, planes of 4 columns, not
+a multiple of 4 (the last unit repeats columns of the one before) and below 4
+(other kernels), partial blocks of 64 units, tiles that span images and end
+inside one, runs of less than a round of tiles, of whole rounds and with tiles
+shared by parts of the rows, the input widths where the tile changes, and the
+widest input.
+"""
+
+import zlib
+
+import numpy as np
+import pytest
+
+from synth import make_layer, densify
+from gpu_util import gpu_run, assert_parity, note, to_gpu, device
+
+pytestmark = pytest.mark.gpu
+
+# (cin, cout, h, w, n, sparsity, k, act)
+FEW = [
+    (16, 16, 2, 2, 1, 0.0, 1, "relu"),       # one unit; rows of two whole batches
+    (5, 3, 1, 1, 1, 0.0, 1, "relu6"),        # H*W below 4
+    (33, 20, 1, 5, 1, 0.7, 1, "none"),       # the second unit repeats 3 columns
+    (72, 96, 7, 7, 5, 0.85, 2, "relu"),      # 65 units: a block of one unit
+    (64, 130, 5, 5, 7, 0.9, 1, "relu6"),
+    (512, 64, 14, 14, 1, 0.9, 1, "relu6"),
+    (1300, 40, 6, 6, 2, 0.95, 1, "none"),    # wider than every staged kernel
+    (128, 256, 8, 8, 2, 0.9, 4, "relu"),
+]
+STRIP = [
+    (16, 20, 64, 64, 9, 0.8, 1, "relu"),       # 9216 units of 64: less than a round, shared by parts
+    (17, 17, 13, 13, 250, 0.5, 1, "none"),     # odd planes, tiles span images, a ragged last tile
+    (79, 48, 32, 32, 130, 0.85, 1, "relu6"),   # the widest 64-unit tile
+    (80, 40, 32, 32, 40, 0.85, 4, "relu"),     # 32-unit tiles, 2 columns a lane
+    (80, 140, 21, 21, 90, 0.8, 1, "none"),     # one workgroup of 16 wavefronts a compute unit
+    (128, 256, 28, 28, 168, 0.9, 1, "relu"),   # the same: two rounds and shared tiles
+    (159, 300, 28, 28, 42, 0.9, 2, "relu6"),   # the widest input there
+    (160, 260, 7, 7, 90, 0.85, 1, "relu"),     # the widest input, 31-unit tiles
+    (161, 260, 7, 7, 90, 0.85, 1, "relu"),     # past it
+    (24, 144, 2, 2, 4200, 0.85, 1, "none"),    # planes of one unit
+]
+
+
+def _check(spec, what):
+    cin, cout, h, w, n, s, k, act = spec
+    layer = make_layer(cin, cout, h, w, n, s, block_rows=k, act=act, seed=zlib.crc32(repr(spec).encode()) % 1000)
+    note("%s %s" % (what, spec))
+    y = gpu_run(layer)
+    assert_parity(layer, y, what=str(spec))
+    assert np.array_equal(y.view(np.uint32), gpu_run(layer, kernel=2).view(np.uint32))
+
+
+@pytest.mark.parametrize("spec", FEW, ids=lambda s: "%d-%d-%dx%d-n%d-s%g-k%d-%s" % s)
+def test_few_columns_match_oracle_and_direct_kernel(spec):
+    _check(spec, "rows few")
+
+
+@pytest.mark.parametrize("spec", STRIP, ids=lambda s: "%d-%d-%dx%d-n%d-s%g-k%d-%s" % s)
+def test_lds_rows_match_oracle_and_direct_kernel(spec):
+    _check(spec, "rows lds")
+
+
+@pytest.mark.parametrize("n", [3, 260])
+def test_rows_without_weights_and_a_long_row(n):
+    """Rows and channels without a stored weight, and one long row (of fewer
+    than the 32 weights from which the direct-load kernel splits rows)."""
+    layer = make_layer(48, 56, 12, 12, n, 0.8, act="none", seed=4)
+    rng = np.random.default_rng(4)
+    rp, ci = [0], []
+    for r in range(layer.cout):
+        s, e = layer.row_ptr[r], layer.row_ptr[r + 1]
+        cols = list(range(31)) if r == 17 else [] if r % 5 == 0 else [c for c in layer.col_idx[s:e] if c % 3]
+        ci += [int(c) for c in cols]
+        rp.append(len(ci))
+    layer.row_ptr, layer.col_idx = np.array(rp, np.int32), np.array(ci, np.int32)
+    layer.values = rng.standard_normal(len(ci)).astype(np.float32)
+    note("rows empty n=%d" % n)
+    y = gpu_run(layer)
+    assert_parity(layer, y, what="empty rows")
+    assert np.array_equal(y.view(np.uint32), gpu_run(layer, kernel=2).view(np.uint32))
+
+
+@pytest.mark.parametrize("hw,n", [((8, 8), 5), ((7, 7), 5), ((1, 2), 5), ((8, 8), 600), ((7, 7), 800)])
+def test_rows_unaligned_pointers(hw, n):
+    """x and y one element off a 16-byte boundary: the same bits, nothing
+    written outside y."""
+    import torch
+    from paper_1911_09723_amd import Plan
+    layer = make_layer(40, 50, hw[0], hw[1], n, 0.8, act="relu", seed=5)
+    note("rows unaligned %s n=%d" % (hw, n))
+    ref = gpu_run(layer)
+    plan = Plan.from_layer(layer)
+    try:
+        flat = to_gpu(np.concatenate([np.zeros(1, np.float32), layer.x.ravel()]))
+        ybuf = torch.full((1 + ref.size + 8,), 7.0, device=device())
+        y = ybuf[1:1 + ref.size].view(ref.shape)
+        plan.run(flat[1:].view(layer.x.shape), y)
+        torch.cuda.synchronize()
+        assert np.array_equal(y.cpu().numpy().view(np.uint32), ref.view(np.uint32))
+        assert float(ybuf[0]) == 7.0 and torch.all(ybuf[1 + ref.size:] == 7.0)
+    finally:
+        plan.close()
+
+
+@pytest.mark.parametrize("hw,n", [((8, 8), 4), ((7, 7), 4), ((1, 1), 4), ((8, 8), 600), ((7, 7), 800)])
+@pytest.mark.parametrize("act", ["relu6", "none"])
+def test_rows_infinities_and_nans_stay_on_their_rows(hw, n, act):
+    """Non-finite inputs reach the rows that store a weight at their channel
+    and no other (padding reads a row of zeros)."""
+    layer = make_layer(70, 45, hw[0], hw[1], n, 0.8, act=act, seed=17)
+    x = layer.x.copy()
+    x[0, 3, 0, 0] = np.inf
+    x[1, 40, -1, -1] = -np.inf
+    x[n - 1, 69, -1, -1] = np.nan
+    x[n - 1, 12, 0, 0] = np.inf
+    note("rows non-finite %s n=%d %s" % (hw, n, act))
+    y = gpu_run(layer, x=x).astype(np.float64)
+    wd = densify(45, 70, 1, layer.row_ptr, layer.col_idx, layer.values)
+    stored = densify(45, 70, 1, layer.row_ptr, layer.col_idx, np.ones_like(layer.values)) > 0
+    finite = np.where(np.isfinite(x), x, 0).astype(np.float64)
+    s = np.einsum("rc,nchw->nrhw", wd, finite) + layer.bias[None, :, None, None]
+    for i, c, r0, c0 in np.argwhere(~np.isfinite(x)):
+        for r in np.flatnonzero(stored[:, c]):
+            s[i, r, r0, c0] += wd[r, c] * float(x[i, c, r0, c0])
+    if act == "relu6":
+        s = np.where(np.isnan(s), 0.0, np.clip(s, 0, 6))  # a NaN clamps to the lower bound
+    else:
+        s = np.where(np.isnan(s), -np.inf, s)
+    assert np.array_equal(np.isfinite(y), np.isfinite(s))
+    ok = np.isfinite(s)
+    assert np.array_equal(y[~ok], s[~ok])
+    # fp32 sums of at most 70 terms, each of size 1
+    assert np.all(np.abs(y[ok] - s[ok]) <= 1e-4)
