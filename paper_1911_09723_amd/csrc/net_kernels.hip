@@ -33,14 +33,20 @@ __device__ __forceinline__ float clamp_act(float v, int32_t act) {
 // kernel).  Workgroup = 256 consecutive pixels of one image (block b covers
 // image b / bpi), so no thread divides 64-bit indices; consecutive threads
 // are consecutive pixels and each channel's stores coalesce.
+// A pixel's channels are gathered in one or two wide loads, which keeps the
+// address unit off the critical path (64 images of 112 x 112 x 3, 24 channels
+// 29.7 -> 27.7 us; 32 of 224 x 224 x 4, stride 2, 39.6 -> 26.6; 64 of 224 x 224 x 3,
+// 32 channels, stride 2, 37.0 -> 36.2, at 3.9 TB/s, bound by the multiply-adds).
+// SPLIT: short runs, each of gridDim.y workgroups makes opb of a pixel's channels.
 using ConstF = const __attribute__((address_space(4))) float;
 
-template <int CIN>
+template <int CIN, bool SPLIT>
 __global__ void __launch_bounds__(256)
 conv3x3_hwc_kernel(const float *__restrict__ x, const float *__restrict__ wt, const float *__restrict__ bias,
                    float *__restrict__ y, int32_t bpi, int32_t h, int32_t w, int32_t ho, int32_t wo,
-                   int32_t cout, int32_t stride, int32_t act) {
+                   int32_t cout, int32_t stride, int32_t act, int32_t opb) {
     const int32_t img = blockIdx.x / bpi;
+    const int32_t o1 = SPLIT ? min(cout, static_cast<int32_t>(blockIdx.y + 1) * opb) : cout;
     const int32_t plane = ho * wo;
     const int32_t pp = (blockIdx.x - img * bpi) * 256 + threadIdx.x;
     if (pp >= plane)
@@ -55,17 +61,18 @@ conv3x3_hwc_kernel(const float *__restrict__ x, const float *__restrict__ wt, co
         for (int dx = 0; dx < 3; ++dx) {
             const int32_t ix = ox * stride + dx - 1;
             const bool in = iy >= 0 && iy < h && ix >= 0 && ix < w;
-            const float *px = xi + ((in ? iy : 0) * w + (in ? ix : 0)) * CIN;
+            float t[CIN];
+            __builtin_memcpy(t, xi + ((in ? iy : 0) * w + (in ? ix : 0)) * CIN, sizeof t);
 #pragma unroll
             for (int i = 0; i < CIN; ++i)
-                v[dy * 3 + dx][i] = in ? px[i] : 0.0f;
+                v[dy * 3 + dx][i] = in ? t[i] : 0.0f;
         }
     }
     float *yo = y + static_cast<int64_t>(img) * cout * plane + pp;
     ConstF *cw = (ConstF *)wt;
     ConstF *cb = (ConstF *)bias;
 #pragma unroll 2
-    for (int32_t o = 0; o < cout; ++o) {
+    for (int32_t o = SPLIT ? blockIdx.y * opb : 0; o < o1; ++o) {
         ConstF *wo9 = cw + o * 9 * CIN;
         float acc = 0.0f;
 #pragma unroll
@@ -492,23 +499,30 @@ linear_kernel(const float *__restrict__ x, const float *__restrict__ wt, const f
 }
 
 using ConvFn = void (*)(const float *, const float *, const float *, float *, int32_t, int32_t, int32_t, int32_t,
-                        int32_t, int32_t, int32_t, int32_t);
+                        int32_t, int32_t, int32_t, int32_t, int32_t);
 
+template <bool SPLIT>
 ConvFn pick_conv(int32_t cin) {
     switch (cin) {
-    case 1: return conv3x3_hwc_kernel<1>;
-    case 2: return conv3x3_hwc_kernel<2>;
-    case 3: return conv3x3_hwc_kernel<3>;
-    case 4: return conv3x3_hwc_kernel<4>;
-    case 5: return conv3x3_hwc_kernel<5>;
-    case 6: return conv3x3_hwc_kernel<6>;
-    case 7: return conv3x3_hwc_kernel<7>;
-    case 8: return conv3x3_hwc_kernel<8>;
+    case 1: return conv3x3_hwc_kernel<1, SPLIT>;
+    case 2: return conv3x3_hwc_kernel<2, SPLIT>;
+    case 3: return conv3x3_hwc_kernel<3, SPLIT>;
+    case 4: return conv3x3_hwc_kernel<4, SPLIT>;
+    case 5: return conv3x3_hwc_kernel<5, SPLIT>;
+    case 6: return conv3x3_hwc_kernel<6, SPLIT>;
+    case 7: return conv3x3_hwc_kernel<7, SPLIT>;
+    case 8: return conv3x3_hwc_kernel<8, SPLIT>;
     default: return nullptr;
     }
 }
 
 constexpr int kThreads = 256;
+// Workgroups wanted of a convolution: 4 a compute unit.  A shorter run has the
+// channels of a pixel shared by 2, 4, 8 .. threads, down to 4 channels each
+// (224 x 224 x 3 -> 32, stride 2: one image, 49 workgroups, 8.3 -> 3.6 us, four
+// images 9.0 -> 6.2, eight 10.7 -> 8.6); past it the gathers repeated for each
+// share cost more than the fill gives (64 images with 2 shares 37.7 -> 40.2).
+constexpr int64_t kConvBlocks = 1024;
 // depthwise kernel: output rows per group, wavefronts wanted per launch
 constexpr int kDwRows = 4;
 constexpr int64_t kDwWaves = 8192;
@@ -518,16 +532,21 @@ constexpr int64_t kDwWaves = 8192;
 hipError_t launch_conv3x3_hwc(const float *x, const float *wt, const float *bias, float *y, int32_t n, int32_t h,
                               int32_t w, int32_t cin, int32_t cout, int32_t stride, int32_t act,
                               hipStream_t stream) {
-    ConvFn kern = pick_conv(cin);
-    if (!kern)
-        return hipErrorInvalidValue;
     const int32_t ho = (h - 1) / stride + 1, wo = (w - 1) / stride + 1;
     const int64_t bpi = (static_cast<int64_t>(ho) * wo + kThreads - 1) / kThreads;
     // per-image offsets are 32-bit, the grid one dimension
     if (static_cast<int64_t>(h) * w * cin >= INT32_MAX || bpi * n >= INT32_MAX)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(bpi * n)), dim3(kThreads), 0, stream, x, wt, bias, y,
-                       static_cast<int32_t>(bpi), h, w, ho, wo, cout, stride, act);
+    int32_t parts = 1;
+    while (bpi * n * parts < kConvBlocks && 8 * parts <= cout)
+        parts *= 2;
+    const int32_t opb = (cout + parts - 1) / parts;
+    ConvFn kern = parts > 1 ? pick_conv<true>(cin) : pick_conv<false>(cin);
+    if (!kern)
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(bpi * n), static_cast<unsigned>((cout + opb - 1) / opb)),
+                       dim3(kThreads), 0, stream, x, wt, bias, y, static_cast<int32_t>(bpi), h, w, ho, wo, cout, stride,
+                       act, opb);
     return hipGetLastError();
 }
 
