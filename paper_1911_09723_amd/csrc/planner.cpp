@@ -700,11 +700,8 @@ Status build_plan(const Input &in_arg, const Options &opt, PackedPlan &p, std::s
         p.rlane_cols = opt.lane_cols;
     }
     p.auto_kernel = opt.kernel == 0;
-    if (p.auto_kernel) {
+    if (p.auto_kernel)
         build_half(in, p);
-        if (opt.split)
-            build_rows(in, p);
-    }
     if (outer_supported(in) && (opt.kernel == 0 || opt.kernel == 4)) {
         build_outer(in, p);
         p.use_outer = opt.kernel == 4;
@@ -786,6 +783,8 @@ Status build_plan(const Input &in_arg, const Options &opt, PackedPlan &p, std::s
         else
             lay_out(INT32_MAX);
     }
+    if (p.auto_kernel && opt.split)
+        build_rows(in, p.split_rows ? split_min : INT32_MAX, p);
     const int32_t nb = bundles_of(static_cast<int32_t>(ents.size()), NB);
     ents.resize(static_cast<size_t>(nb) * NB, Entry{-1, -1});
     std::vector<int32_t> bsteps(nb, 0);
@@ -1454,12 +1453,13 @@ void build_half(const Input &in, PackedPlan &p) {
         }
 }
 
-void build_rows(const Input &in, PackedPlan &p) {
+void build_rows(const Input &in, int32_t split_min, PackedPlan &p) {
     if (in.storage != 0 || in.dw_stride)
         return;
     const int32_t k = in.block_rows, cout = in.cout;
     auto begin = [&](int32_t r) { return in.row_ptr[r / k]; };
     auto len = [&](int32_t r) { return in.row_ptr[r / k + 1] - in.row_ptr[r / k]; };
+    auto pieces = [&](int32_t r) { return len(r) >= split_min ? 2 : 1; };
     p.tbias.assign(static_cast<size_t>(cout), 0.0f);
     if (in.bias)
         std::copy(in.bias, in.bias + cout, p.tbias.begin());
@@ -1478,10 +1478,21 @@ void build_rows(const Input &in, PackedPlan &p) {
             std::memcpy(&d[2 * e + 1], &val[static_cast<int64_t>(e) * k], 4);
         }
     }
+    const std::vector<int32_t> start(p.trow_ptr);
+    int32_t split_rows = 0;
+    for (int32_t r = 0; r < cout; ++r)
+        if (pieces(r) == 2) {
+            p.trow_ptr[r] |= kRowSplit;
+            ++split_rows;
+        }
     if (in.cin > kRowMaxCin)
         return;
     // rows to lists, then lists to wavefronts (a row costs its groups and its epilogue)
-    auto groups = [&](int32_t r) { return std::max(1, (len(r) + kGroupRecs - 1) / kGroupRecs); };
+    auto piece_len = [&](int32_t r, int32_t i) { return pieces(r) == 1 ? len(r) : (len(r) + 1 - i) / 2; };
+    auto piece_groups = [&](int32_t r, int32_t i) {
+        return std::max(1, (piece_len(r, i) + kGroupRecs - 1) / kGroupRecs);
+    };
+    auto groups = [&](int32_t r) { return piece_groups(r, 0) + (pieces(r) == 2 ? piece_groups(r, 1) : 0); };
     constexpr int32_t kWaves = 8, kPer = kRowLists / kWaves;
     std::vector<int32_t> order(cout);
     std::iota(order.begin(), order.end(), 0);
@@ -1515,7 +1526,7 @@ void build_rows(const Input &in, PackedPlan &p) {
     for (int32_t r = 0; r < cout; ++r)
         total += groups(r);
     p.gent.assign(static_cast<size_t>(total + 2) * 2 * kGroupRecs, 0u);
-    p.gdesc.assign((static_cast<size_t>(cout) + 1) * 4, 0u);
+    p.gdesc.assign((static_cast<size_t>(cout) + split_rows + 1) * 4, 0u);
     p.glist.clear();
     size_t at = 0;   // group
     size_t row = 0;  // description
@@ -1525,21 +1536,25 @@ void build_rows(const Input &in, PackedPlan &p) {
             p.glist.push_back(static_cast<int32_t>(at));
             std::sort(rows[l].begin(), rows[l].end());
             for (int32_t r : rows[l]) {
-                uint32_t *d = &p.gdesc[4 * row++];
-                d[0] = static_cast<uint32_t>(r);
-                d[1] = static_cast<uint32_t>(groups(r));
-                std::memcpy(&d[2], &p.tbias[r], 4);
-                const uint32_t *e = p.tent.data() + 2 * static_cast<size_t>(p.trow_ptr[r]);
-                const int32_t n = len(r), ng = groups(r);
-                uint32_t *g = &p.gent[at * 2 * kGroupRecs];
-                for (int32_t i = 0; i < n; ++i) {
-                    uint32_t *at_i = g + i / kGroupRecs * 2 * kGroupRecs + i % kGroupRecs;
-                    at_i[0] = e[2 * i];
-                    at_i[kGroupRecs] = e[2 * i + 1];
+                const int32_t step = pieces(r);
+                for (int32_t piece = 0; piece < step; ++piece) {
+                    const int32_t n = piece_len(r, piece), ng = piece_groups(r, piece);
+                    uint32_t *d = &p.gdesc[4 * row++];
+                    d[0] = static_cast<uint32_t>(r);
+                    d[1] = static_cast<uint32_t>(ng);
+                    std::memcpy(&d[2], &p.tbias[r], 4);
+                    d[3] = static_cast<uint32_t>(step == 1 ? 0 : 1 + piece);
+                    const uint32_t *e = p.tent.data() + 2 * (static_cast<size_t>(start[r]) + piece);
+                    uint32_t *g = &p.gent[at * 2 * kGroupRecs];
+                    for (int32_t i = 0; i < n; ++i) {
+                        uint32_t *at_i = g + i / kGroupRecs * 2 * kGroupRecs + i % kGroupRecs;
+                        at_i[0] = e[2 * step * i];
+                        at_i[kGroupRecs] = e[2 * step * i + 1];
+                    }
+                    for (int32_t i = n; i < ng * kGroupRecs; ++i)  // padding reads the row of zeros, weights are 0
+                        g[i / kGroupRecs * 2 * kGroupRecs + i % kGroupRecs] = static_cast<uint32_t>(in.cin);
+                    at += ng;
                 }
-                for (int32_t i = n; i < ng * kGroupRecs; ++i)  // padding reads the row of zeros, weights are 0
-                    g[i / kGroupRecs * 2 * kGroupRecs + i % kGroupRecs] = static_cast<uint32_t>(in.cin);
-                at += ng;
             }
         }
     p.glist.push_back(static_cast<int32_t>(row));

@@ -229,17 +229,23 @@ constexpr int64_t kHalfMaxFragBytes = 16 << 20;     // dense weights kept beside
 
 // Row kernels (fp32, where the automatic choice takes them): a wavefront sums
 // one output channel at a time over many columns.  trow_ptr, tent and tbias as
-// for the half kernel (the kernel for few columns walks them).  The LDS kernel
+// for the half kernel (the kernel for few columns walks them).  A row that the
+// strip plan packs as two pieces is summed as two here as well, its even and its
+// odd weights (the same bits; one chain of them all has 10% more rounding error
+// on heavy-tailed layers): kRowSplit marks it in trow_ptr, and in the streams
+// below it is two entries, one after the other.  The LDS kernel
 // walks streams of groups of kGroupRecs stored weights: a row's weights in
 // ascending channel, the last group padded with weight 0 at channel cin (a row
 // of zeros in LDS), at least one group.  A group is kGroupRecs channels, then
 // their weights (fp32 bits).  Rows are dealt to kRowLists lists, longest first
 // to the least loaded, and the lists to the wavefronts of a workgroup the same
 // way, kRowLists / 8 each, so that lists w * kRowLists / 8 .. are wavefront
-// w's; inside a list rows ascend.  gdesc holds 4 words per row in list order:
-// output channel, groups, bias (fp32 bits), 0; list l has the rows glist[2 l]
+// w's; inside a list rows ascend.  gdesc holds 4 words per entry in list order:
+// output channel, groups, bias (fp32 bits), piece (0 a whole row, 1 and 2 the
+// pieces of one); list l has the entries glist[2 l]
 // .. glist[2 l + 2] of it and starts at group glist[2 l + 1].  The streams end
 // with two padding groups and gdesc with a zero entry (read ahead).
+constexpr int32_t kRowSplit = INT32_MIN;
 constexpr int32_t kGroupRecs = 4;
 constexpr int32_t kRowLists = 64;
 constexpr int32_t kRowMaxCin = 160;  // a tile of X fits in LDS, and the next one in registers
@@ -442,7 +448,8 @@ void build_outer(const Input &in, PackedPlan &p);
 void build_half(const Input &in, PackedPlan &p);
 // Build the row kernels' arrays (fields t*, g* of PackedPlan), when the layer is
 // in their range (fp32 storage, no depthwise stage; g*: cin <= kRowMaxCin).
-void build_rows(const Input &in, PackedPlan &p);
+// Rows of at least split_min weights are in two pieces.
+void build_rows(const Input &in, int32_t split_min, PackedPlan &p);
 // Rebuild block-CSR arrays from the lockstep kernel's records, checking their
 // structure (lockstep padding, ascending channels, offsets, wave lists).
 // E_FORMAT with `err` set when inconsistent or absent.

@@ -330,7 +330,7 @@ void fill_device_geometry(spconv_plan_s *pl) {
     d.groups = h.glist.empty() ? 0 : h.glist.back();
     d.max_row = 0;
     for (size_t r = 0; r + 1 < h.trow_ptr.size(); ++r)
-        d.max_row = std::max(d.max_row, h.trow_ptr[r + 1] - h.trow_ptr[r]);
+        d.max_row = std::max(d.max_row, (h.trow_ptr[r + 1] & ~spconv::kRowSplit) - (h.trow_ptr[r] & ~spconv::kRowSplit));
     d.nnz = h.trow_ptr.empty() ? 0 : h.trow_ptr.back();
 }
 

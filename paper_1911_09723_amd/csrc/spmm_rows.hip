@@ -30,7 +30,8 @@
 // plane whose size is not a multiple of 4 starts early and repeats columns of
 // the one before (the same sums, the same bits), so every load and store is
 // whole.  Each output is summed in ascending input channel from zero with
-// fused multiply-adds, the bias last: the bits of the other kernels.
+// fused multiply-adds (a row that the strip plan splits as the sum of its two
+// pieces), the bias last: the bits of the other kernels.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -72,34 +73,24 @@ struct RArgs {
 constexpr int kRowWaves = 4;
 constexpr int kRowDepth = 8;  // loads per batch; two batches in flight
 
-__global__ void __launch_bounds__(64 * kRowWaves) rows_kernel(RArgs a) {
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int32_t item = static_cast<int32_t>(blockIdx.x) * kRowWaves + wave;
-    const int32_t row = item / a.blocks;
-    if (row >= a.cout)
-        return;
-    const int32_t g = min((item - row * a.blocks) * 64 + lane, a.all - 1);  // lanes past the end repeat the last unit
-    const int32_t im = g / a.units;
-    const int32_t p = min(4 * (g - im * a.units), a.hw - 4);
-    const float *xb = a.x + static_cast<int64_t>(im) * a.cin * a.hw + p;
-    const ConstI *rp = reinterpret_cast<const ConstI *>(reinterpret_cast<uintptr_t>(a.row_ptr));
-    const int32_t t0 = rp[row], n = rp[row + 1] - t0;
-    // weight t: word 2 t its channel, 2 t + 1 its bits; a batch's in one scalar load
-    const ConstI *ent = reinterpret_cast<const ConstI *>(reinterpret_cast<uintptr_t>(a.ent)) + 2 * static_cast<int64_t>(t0);
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
+// The sum over n stored weights of one row (ent: weight t's channel in word 2 t,
+// its bits in 2 t + 1; a batch's in one scalar load) times X at xb; P = 2: of the
+// even and of the odd ones apart, then both.
+template <int P>
+__device__ __forceinline__ f4 row_sum(const ConstI *ent, int32_t n, const float *xb, int32_t hw) {
+    f4 acc[P] = {};
     constexpr int D = kRowDepth;
     auto load = [&](const u16v &r, f4(&v)[D]) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < D; ++i)
-            __builtin_memcpy(&v[i], xb + static_cast<int64_t>(static_cast<int32_t>(r[2 * i])) * a.hw, 16);
+            __builtin_memcpy(&v[i], xb + static_cast<int64_t>(static_cast<int32_t>(r[2 * i])) * hw, 16);
     };
     auto sum = [&](const u16v &r, const f4(&v)[D]) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < D; ++i)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                acc[e] = __builtin_fmaf(__uint_as_float(r[2 * i + 1]), v[i][e], acc[e]);
+                acc[i % P][e] = __builtin_fmaf(__uint_as_float(r[2 * i + 1]), v[i][e], acc[i % P][e]);
     };
     const int32_t batches = n / D;
     f4 va[D], vb[D];
@@ -126,15 +117,42 @@ __global__ void __launch_bounds__(64 * kRowWaves) rows_kernel(RArgs a) {
 #pragma unroll
     for (int i = 0; i < D - 1; ++i)
         if (done + i < n)
-            __builtin_memcpy(&vb[i], xb + static_cast<int64_t>(ent[2 * (done + i)]) * a.hw, 16);
+            __builtin_memcpy(&vb[i], xb + static_cast<int64_t>(ent[2 * (done + i)]) * hw, 16);
 #pragma unroll
     for (int i = 0; i < D - 1; ++i)
         if (done + i < n) {
             const float w = __int_as_float(ent[2 * (done + i) + 1]);
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                acc[e] = __builtin_fmaf(w, vb[i][e], acc[e]);
+                acc[i % P][e] = __builtin_fmaf(w, vb[i][e], acc[i % P][e]);
         }
+    if constexpr (P == 2)
+        acc[0] += acc[1];
+    return acc[0];
+}
+
+// SPLIT: the plan has rows in two pieces.
+template <bool SPLIT>
+__global__ void __launch_bounds__(64 * kRowWaves) rows_kernel(RArgs a) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int32_t item = static_cast<int32_t>(blockIdx.x) * kRowWaves + wave;
+    const int32_t row = item / a.blocks;
+    if (row >= a.cout)
+        return;
+    const int32_t g = min((item - row * a.blocks) * 64 + lane, a.all - 1);  // lanes past the end repeat the last unit
+    const int32_t im = g / a.units;
+    const int32_t p = min(4 * (g - im * a.units), a.hw - 4);
+    const float *xb = a.x + static_cast<int64_t>(im) * a.cin * a.hw + p;
+    const ConstI *rp = reinterpret_cast<const ConstI *>(reinterpret_cast<uintptr_t>(a.row_ptr));
+    const int32_t r0 = rp[row], t0 = SPLIT ? r0 & ~kRowSplit : r0;
+    const int32_t n = (SPLIT ? rp[row + 1] & ~kRowSplit : rp[row + 1]) - t0;
+    const ConstI *ent = reinterpret_cast<const ConstI *>(reinterpret_cast<uintptr_t>(a.ent)) + 2 * static_cast<int64_t>(t0);
+    f4 acc;
+    if (SPLIT && (r0 & kRowSplit))
+        acc = row_sum<2>(ent, n, xb, a.hw);
+    else
+        acc = row_sum<1>(ent, n, xb, a.hw);
     const ConstF *bias = reinterpret_cast<const ConstF *>(reinterpret_cast<uintptr_t>(a.bias));
     f4 v;
 #pragma unroll
@@ -170,8 +188,10 @@ typedef uint32_t u4v __attribute__((ext_vector_type(4), aligned(4)));
 using ConstU4 = __attribute__((address_space(4))) const u4v;
 typedef unsigned int vu4 __attribute__((vector_size(16)));
 
-// V columns a lane: 4 / V lanes a unit, tiles of up to 16 V units.
-template <int V>
+// V columns a lane: 4 / V lanes a unit, tiles of up to 16 V units.  SPLIT: the
+// plan has rows in two pieces (a variant of its own: the test at each row's end
+// costs 128 -> 128 @ 56 x 56, batch 64, 2 us of 62).
+template <int V, bool SPLIT>
 __global__ void __launch_bounds__(1024) strip_rows_kernel(SArgs a) {
     constexpr int LPU = 4 / V;
     constexpr int TU = 64 / LPU;  // units of a row of lanes
@@ -262,7 +282,7 @@ __global__ void __launch_bounds__(1024) strip_rows_kernel(SArgs a) {
             fetch(item);
         if (rows > 0) {
             fv xa[G], xb[G];
-            fv acc = {};
+            fv acc = {}, first = {};
             int32_t left = static_cast<int32_t>(d[1]);
             auto read = [&](const u4v &o, fv(&x)[G]) __attribute__((always_inline)) {
 #pragma unroll
@@ -291,18 +311,23 @@ __global__ void __launch_bounds__(1024) strip_rows_kernel(SArgs a) {
                     for (int e = 0; e < V; ++e)
                         acc[e] = __builtin_fmaf(__uint_as_float(w[j]), x[j][e], acc[e]);
                 if (--left == 0) {
-                    const float bias = __uint_as_float(d[2]);
-                    vv o;
+                    if (SPLIT && d[3] == 1) {  // the even weights of a split row: its odd ones follow
+                        first = acc;
+                    } else {
+                        if (SPLIT && d[3] == 2)
+                            acc = first + acc;
+                        const float bias = __uint_as_float(d[2]);
+                        vv o;
 #pragma unroll
-                    for (int e = 0; e < V; ++e) {
-                        o[e] = __float_as_uint(__builtin_amdgcn_fmed3f(acc[e] + bias, a.lo, a.hi));
-                        acc[e] = 0.0f;
+                        for (int e = 0; e < V; ++e)
+                            o[e] = __float_as_uint(__builtin_amdgcn_fmed3f(acc[e] + bias, a.lo, a.hi));
+                        const int32_t so = static_cast<int32_t>(d[0]) * a.hw * 4;
+                        if constexpr (V == 4)
+                            __builtin_amdgcn_raw_buffer_store_b128(o, ry, yo, so, 0);
+                        else
+                            __builtin_amdgcn_raw_buffer_store_b64(o, ry, yo, so, 0);
                     }
-                    const int32_t so = static_cast<int32_t>(d[0]) * a.hw * 4;
-                    if constexpr (V == 4)
-                        __builtin_amdgcn_raw_buffer_store_b128(o, ry, yo, so, 0);
-                    else
-                        __builtin_amdgcn_raw_buffer_store_b64(o, ry, yo, so, 0);
+                    acc = fv{};
                     ++desc;
                     d = *desc;
                     left = static_cast<int32_t>(d[1]);
@@ -397,7 +422,7 @@ hipError_t launch_rows(const DevicePlan &p, const float *x, float *y, int32_t m,
     a.lo = p.act == 0 ? -__builtin_huge_valf() : 0.0f;
     a.hi = p.act == 2 ? 6.0f : __builtin_huge_valf();
     const int64_t items = static_cast<int64_t>(a.blocks) * p.cout;
-    hipLaunchKernelGGL(rows_kernel, dim3(static_cast<unsigned>((items + kRowWaves - 1) / kRowWaves)),
+    hipLaunchKernelGGL(p.splits ? rows_kernel<true> : rows_kernel<false>, dim3(static_cast<unsigned>((items + kRowWaves - 1) / kRowWaves)),
                        dim3(64 * kRowWaves), 0, stream, a);
     return hipGetLastError();
 }
@@ -410,8 +435,10 @@ hipError_t prepare_strip_rows(const DevicePlan &) {
     const uint64_t bit = dev < 64 ? uint64_t(1) << dev : 0;
     if (done.load() & bit)
         return hipSuccess;
-    for (const void *k : {reinterpret_cast<const void *>(strip_rows_kernel<2>),
-                          reinterpret_cast<const void *>(strip_rows_kernel<4>)}) {
+    for (const void *k : {reinterpret_cast<const void *>(strip_rows_kernel<2, false>),
+                          reinterpret_cast<const void *>(strip_rows_kernel<4, false>),
+                          reinterpret_cast<const void *>(strip_rows_kernel<2, true>),
+                          reinterpret_cast<const void *>(strip_rows_kernel<4, true>)}) {
         const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
         if (e != hipSuccess)
             return e;
@@ -470,7 +497,9 @@ hipError_t launch_strip_rows(const DevicePlan &p, const float *x, float *y, int3
         a.parts *= 2;
     a.nxcd = 8;
     const int64_t grid = a.rounds > 0 ? slots : (static_cast<int64_t>(a.rest) * a.parts + 7) / 8 * 8;
-    hipLaunchKernelGGL(v == 4 ? strip_rows_kernel<4> : strip_rows_kernel<2>, dim3(static_cast<unsigned>(grid)),
+    const auto kernel = p.splits ? (v == 4 ? strip_rows_kernel<4, true> : strip_rows_kernel<2, true>)
+                                 : (v == 4 ? strip_rows_kernel<4, false> : strip_rows_kernel<2, false>);
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(grid)),
                        dim3(64 * waves), (p.cin + 1) * a.row_bytes, stream, a);
     return hipGetLastError();
 }

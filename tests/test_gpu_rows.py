@@ -137,3 +137,33 @@ def test_rows_infinities_and_nans_stay_on_their_rows(hw, n, act):
     assert np.array_equal(y[~ok], s[~ok])
     # fp32 sums of at most 70 terms, each of size 1
     assert np.all(np.abs(y[ok] - s[ok]) <= 1e-4)
+
+
+# heavy-tailed layers whose strip plan packs rows as two pieces (cin, cout, h, w, n, sparsity, act)
+SPLIT = [
+    (128, 64, 14, 14, 1, 0.85, "none"),     # few columns
+    (144, 200, 7, 7, 1, 0.85, "relu"),
+    (100, 100, 13, 13, 1, 0.85, "none"),
+    (600, 64, 14, 14, 1, 0.97, "relu6"),
+    (144, 24, 56, 56, 12, 0.85, "none"),    # LDS tiles, 2 columns a lane
+    (96, 64, 28, 28, 48, 0.85, "relu"),
+    (120, 32, 21, 21, 60, 0.85, "none"),    # odd planes
+]
+
+
+@pytest.mark.parametrize("spec", SPLIT, ids=lambda s: "%d-%d-%dx%d-n%d-s%g-%s" % s)
+def test_split_rows_keep_the_strip_kernels_sums(spec):
+    """The even and the odd weights of a split row are summed apart, as in the
+    strip kernel (option 1): the same bits, so no more rounding error."""
+    from paper_1911_09723_amd import Plan
+    cin, cout, h, w, n, s, act = spec
+    layer = make_layer(cin, cout, h, w, n, s, pattern="beta", act=act, seed=cin * 7 + cout)
+    plan = Plan.from_layer(layer)
+    try:
+        assert plan.info()["split_rows"] > 0, "the case must split at least one row"
+    finally:
+        plan.close()
+    note("rows split %s" % (spec,))
+    y = gpu_run(layer)
+    assert_parity(layer, y, what=str(spec))
+    assert np.array_equal(y.view(np.uint32), gpu_run(layer, kernel=1).view(np.uint32))
