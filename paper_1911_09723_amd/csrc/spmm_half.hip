@@ -340,7 +340,10 @@ __global__ void __launch_bounds__(1024) half_kernel(HArgs a) {
                             o[e] = __builtin_bit_cast(uint16_t, static_cast<_Float16>(v0)) |
                                    static_cast<uint32_t>(__builtin_bit_cast(uint16_t, static_cast<_Float16>(v1))) << 16;
                         }
-                        const int32_t so = 2 * (row0 + r) * a.hw;
+                        // (a row past the last is dropped by its lanes' offsets, which are
+                        // checked against what the scalar offset leaves of the resource:
+                        // that one stays inside it)
+                        const int32_t so = 2 * min(row0 + r, a.cout - 1) * a.hw;
                         if constexpr (VEC) {
                             typedef unsigned int vu2 __attribute__((vector_size(8)));
                             __builtin_amdgcn_raw_buffer_store_b64(vu2{o[0], o[1]}, ry,

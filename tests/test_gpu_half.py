@@ -73,6 +73,27 @@ def test_half_alignment_and_batch_do_not_change_bits(hw):
         plan.close()
 
 
+# output channels one to three past a row tile, and second row tiles wholly past
+# the last channel (two tiles a group, inputs of more than 320 channels)
+@pytest.mark.parametrize("cin,cout", [(32, 33), (32, 18), (96, 3), (300, 17), (352, 40), (352, 33), (640, 16)])
+def test_half_rows_past_the_last_channel_are_not_stored(cin, cout):
+    """Whole units of the last image, 16-byte aligned: nothing behind y changes."""
+    import torch
+    from paper_1911_09723_amd import Plan
+    layer = make_layer(cin, cout, 8, 8, 1, 0.8, storage="f16", act="none", seed=cin + cout)
+    note("half rows past the last %d -> %d" % (cin, cout))
+    plan = Plan.from_layer(layer)
+    try:
+        ybuf = torch.full((cout * 64 + 64 * 64,), 7.0, dtype=torch.float16, device=device())
+        y = ybuf[:cout * 64].view(1, cout, 8, 8)
+        plan.run(to_gpu(layer.x), y)
+        torch.cuda.synchronize()
+        assert_parity(layer, y.cpu().numpy(), what="%d -> %d" % (cin, cout))
+        assert torch.all(ybuf[cout * 64:] == 7.0)
+    finally:
+        plan.close()
+
+
 @pytest.mark.parametrize("hw", [(8, 8), (7, 7), (1, 1)])
 @pytest.mark.parametrize("act", ["relu6", "none"])
 def test_half_infinities_and_nans_stay_on_their_rows(hw, act):
