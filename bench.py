@@ -171,13 +171,14 @@ def time_variant(layer, steps, warmup, sets, dw=None, **options):
     torch.cuda.synchronize()
     kern_ms = [a.elapsed_time(b) for a, b in ev]
     info = plan.info()
+    run_kernel = plan.run_kernel(n, h, w)
     flags = plan.check(clear=True)
     plan.close()
     if flags:
         raise RuntimeError("a bounded wait gave up during the timed launches (error word %d)" % flags)
     del xs, ys
     torch.cuda.empty_cache()
-    return dict(region_ms=region_ms, wall_s=wall, kernel_ms=kern_ms, info=info, forced_kernel=options.get("kernel"))
+    return dict(region_ms=region_ms, wall_s=wall, kernel_ms=kern_ms, info=info, run_kernel=run_kernel)
 
 
 def time_network(batch, steps, warmup, graph=True):
@@ -416,31 +417,16 @@ def summarize(layer, r, dw=False):
         "plan": {k: r["info"][k] for k in ("kernel", "group_lanes", "tile_cols", "waves", "lds_bytes", "slots",
                                            "max_parts", "indexed_min_cols")},
     }
-    # the kernel the runs took, as spconv_run chooses it: the half kernel (fp16
-    # layers up to its widest input), outer-product, then
-    # register-indexed (forced, or automatic for this many columns), else the
-    # plan's LDS-strip or direct-load kernel; automatic fp32 runs of few columns
-    # or up to 160 input channels may take a row kernel instead
-    cols = layer.n * layer.hw
-    imc = r["info"]["indexed_min_cols"]
-    omc = r["info"]["outer_min_cols"]
-    forced = r.get("forced_kernel")
-    if forced in (None, 0) and layer.storage == "f16" and layer.cin <= 1216 and not r["info"]["dw_stride"]:
-        run = "half"
-    elif forced == 4 or (forced in (None, 0) and omc > 0 and cols >= omc):
-        run = "outer"
-    elif forced == 3 or (forced in (None, 0) and imc > 0 and cols >= imc):
-        run = "indexed"
-    else:
-        run = "direct" if r["info"]["kernel"] == 1 else "strip"
-        if forced in (None, 0) and layer.storage == "f32" and (layer.cin <= 160 or cols <= 8192):
-            run += " or rows"
-    out["plan"]["kernel_run"] = run
-    out["plan"]["outer_min_cols"] = omc
+    out["plan"]["kernel_run"] = r["run_kernel"]
+    out["plan"]["outer_min_cols"] = r["info"]["outer_min_cols"]
     if layer.storage == "f16":
-        # fp16 plans round W to fp16 but keep it as fp32 in device memory: the
-        # weights move 4 bytes per value, not the 2 alg_bytes counts
-        out["device_weight_extra_bytes"] = 2.0 * layer.nnz
+        # alg_bytes counts 2 bytes a stored weight.  The half kernel reads W as
+        # dense fp16 tiles of 16 x 32, the others read the stored weights in fp32
+        if r["run_kernel"] == "half":
+            dense = 2.0 * (-(-layer.cout // 32) * 32) * (-(-layer.cin // 32) * 32)
+            out["device_weight_extra_bytes"] = dense - 2.0 * layer.nnz
+        else:
+            out["device_weight_extra_bytes"] = 2.0 * layer.nnz
     return out
 
 
@@ -538,7 +524,7 @@ def traffic_summary(fetch_dir, write_dir, commands, out_base):
     lines += ["", "| kernel | counter | KiB/dispatch | scaled MB |", "|---|---|---|---|"]
     for c in ("FETCH_SIZE", "WRITE_SIZE"):
         for k, v in out[c]["kernels"].items():
-            m = re.search(r"(spmm_\w+|outer_kernel)<[^>]*>", k)
+            m = re.search(r"(spmm_\w+|outer_kernel|half_kernel|(?:strip_)?rows_kernel)<[^>]*>", k)
             lines.append("| `%s` | %s | %.0f | %.2f |" % (m.group(0) if m else k, c, v["kib_per_dispatch"],
                                                           v["bytes_scaled"] / 1e6))
     if "bytes_per_launch" in out:

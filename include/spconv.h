@@ -426,6 +426,28 @@ typedef struct {
 /* Describe a plan.  Host only; does not touch the device. */
 SPCONV_API spconv_status spconv_plan_get_info(spconv_plan plan, spconv_plan_info *info);
 
+/* The kernels that spconv_run launches (1 to 5: numbered as spconv_options.kernel). */
+typedef enum {
+    SPCONV_RUN_NONE = 0,     /* an empty run */
+    SPCONV_RUN_STRIP = 1,    /* LDS-strip kernel */
+    SPCONV_RUN_DIRECT = 2,   /* direct-load kernel */
+    SPCONV_RUN_INDEXED = 3,  /* register-indexed kernel */
+    SPCONV_RUN_OUTER = 4,    /* lockstep kernel: outer products (1 x 4 blocks) or its vector mode */
+    SPCONV_RUN_PASSES = 5,   /* channel-range passes */
+    SPCONV_RUN_HALF = 6,     /* fp16 on the matrix cores, W as dense fragments */
+    SPCONV_RUN_ROWS = 7,     /* fp32, a wavefront per output channel (few columns) */
+    SPCONV_RUN_LDS_ROWS = 8  /* fp32, output channels one at a time over tiles of X in LDS */
+} spconv_run_kernel;
+
+/*
+ * The kernel (spconv_run_kernel) that spconv_run takes for this plan and size.
+ * It does not depend on the addresses of x and y.  Host only; for a host-only
+ * plan the answer is the one for a device of 256 compute units.  Errors:
+ * SPCONV_E_ARG (NULL argument, negative size), SPCONV_E_SHAPE (2^31 columns or
+ * more); sizes that only spconv_run refuses are answered.
+ */
+SPCONV_API spconv_status spconv_plan_run_kernel(spconv_plan plan, int32_t n, int32_t h, int32_t w, int32_t *kernel);
+
 /*
  * Reconstruct the plan's weights from its packed host image, in the input's
  * block-CSR form: row_ptr[cout/k + 1], col_idx[nnzb], values[nnzb * k] (each

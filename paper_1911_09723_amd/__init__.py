@@ -30,6 +30,7 @@ from .spconv import (  # noqa: F401
     spconv_plan_create_static,
     SPCONV_STATIC_PLAN_BYTES,
     spconv_plan_get_info,
+    spconv_plan_run_kernel,
     spconv_plan_unpack,
     spconv_plan_unpack_interleaved,
     spconv_plan_unpack_indexed,

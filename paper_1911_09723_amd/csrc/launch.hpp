@@ -79,12 +79,12 @@ struct DevicePlan {
     const float *tbias = nullptr;
     const int32_t *trow_ptr = nullptr;
     const uint32_t *tent = nullptr;
-    // row kernels (planner.hpp); trow_ptr null: the plan has none, glist null:
-    // no streams
+    // row kernels (planner.hpp)
+    bool rows = false;           // the plan has them
     const uint32_t *gent = nullptr;
     const uint32_t *gdesc = nullptr;
     const int32_t *glist = nullptr;
-    int32_t groups = 0;          // of the streams
+    int32_t groups = 0;          // of the streams (0: the plan has none)
     int32_t max_row = 0;         // stored weights of the longest output channel
     int32_t nnz = 0;             // and of all
     // a pass over one channel range of a wider input (spconv_api.cpp): X's

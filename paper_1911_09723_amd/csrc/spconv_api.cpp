@@ -40,6 +40,7 @@ namespace {
 thread_local std::string g_err;
 
 constexpr int32_t kKernelPasses = 5;    // kernel option: channel-range passes
+constexpr int32_t kHostOnlyCus = 256;   // compute units that spconv_plan_run_kernel answers for without a device
 constexpr int32_t kPassChannels = 512;  // most input channels per pass (its LDS strip fits)
 
 // The static device array of spconv_plan_create_static: one per GPU (each
@@ -159,6 +160,8 @@ spconv_status upload(spconv_plan_s *pl, bool use_static) {
         // without these the image may fit: the plan then runs the other kernels
         dense = false;
         pl->dev.hkb = 0;
+        pl->dev.rows = false;
+        pl->dev.groups = 0;
         for (int i = kDenseParts; i < kParts; ++i)
             parts[i].bytes = 0;
         layout();
@@ -240,13 +243,9 @@ spconv_status upload(spconv_plan_s *pl, bool use_static) {
     d.tbias = reinterpret_cast<const float *>(base + parts[27].off);
     d.trow_ptr = reinterpret_cast<const int32_t *>(base + parts[28].off);
     d.tent = reinterpret_cast<const uint32_t *>(base + parts[29].off);
-    if (!dense)
-        d.trow_ptr = nullptr;
-    if (dense && !h.glist.empty()) {
-        d.gent = reinterpret_cast<const uint32_t *>(base + parts[30].off);
-        d.gdesc = reinterpret_cast<const uint32_t *>(base + parts[31].off);
-        d.glist = reinterpret_cast<const int32_t *>(base + parts[32].off);
-    }
+    d.gent = reinterpret_cast<const uint32_t *>(base + parts[30].off);
+    d.gdesc = reinterpret_cast<const uint32_t *>(base + parts[31].off);
+    d.glist = reinterpret_cast<const int32_t *>(base + parts[32].off);
     return SPCONV_OK;
 }
 
@@ -327,11 +326,34 @@ void fill_device_geometry(spconv_plan_s *pl) {
     d.ozrow = h.ozrow;
     d.ooff_bytes = static_cast<int32_t>(h.ooff.size() * sizeof(uint32_t));
     d.hkb = h.hkb;
+    d.rows = h.storage == 0 && !h.trow_ptr.empty();
     d.groups = h.glist.empty() ? 0 : h.glist.back();
     d.max_row = 0;
     for (size_t r = 0; r + 1 < h.trow_ptr.size(); ++r)
         d.max_row = std::max(d.max_row, (h.trow_ptr[r + 1] & ~spconv::kRowSplit) - (h.trow_ptr[r] & ~spconv::kRowSplit));
     d.nnz = h.trow_ptr.empty() ? 0 : h.trow_ptr.back();
+}
+
+// The kernel that a run of `images` output planes of hw columns takes (image_bytes:
+// the larger of one image of x and of y).
+spconv_run_kernel choose_kernel(const spconv_plan_s *pl, const spconv::DevicePlan &d, int64_t images, int64_t hw,
+                                int64_t image_bytes) {
+    const int64_t m = images * hw;
+    // the automatic choices: a wavefront per output channel for few columns,
+    // dense fragments (fp16), whole rows over LDS tiles for many columns
+    if (spconv::rows_pay(d, images, hw))
+        return SPCONV_RUN_ROWS;
+    if (!pl->passes.empty())
+        return SPCONV_RUN_PASSES;
+    if (d.hkb > 0)
+        return SPCONV_RUN_HALF;
+    if (spconv::strip_rows_pay(d, images, hw, image_bytes))
+        return SPCONV_RUN_LDS_ROWS;
+    if (d.use_outer || (d.outer_min_cols > 0 && m >= d.outer_min_cols))
+        return SPCONV_RUN_OUTER;
+    if (d.use_indexed || (d.indexed_min_cols > 0 && m >= d.indexed_min_cols))
+        return SPCONV_RUN_INDEXED;
+    return d.kernel == spconv::KERNEL_DIRECT ? SPCONV_RUN_DIRECT : SPCONV_RUN_STRIP;
 }
 
 bool ranges_overlap(const void *a, size_t abytes, const void *b, size_t bbytes) {
@@ -432,7 +454,7 @@ spconv_status create_plan(spconv_plan *out, const spconv::Input &in, const spcon
                 pe = spconv::prepare_outer(pl->dev);
             if (pe == hipSuccess && pl->dev.hkb > 0)
                 pe = spconv::prepare_half(pl->dev);
-            if (pe == hipSuccess && pl->dev.glist)
+            if (pe == hipSuccess && pl->dev.groups > 0)
                 pe = spconv::prepare_strip_rows(pl->dev);
             pl->dev.indexed_min_cols = indexed_min_cols(pl->host, pl->dev);
             pl->dev.outer_min_cols = outer_min_cols(pl->host, pl->dev);
@@ -759,15 +781,12 @@ spconv_status spconv_run(spconv_plan plan, const void *x, void *y, int32_t n, in
     const int64_t qv = 16 / static_cast<int64_t>(e);  // columns in one 16-byte vector
     const int32_t vec = (hw % qv == 0) && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
                         reinterpret_cast<uintptr_t>(y) % 16 == 0;
-    // the automatic choices that depend on the run's size: a wavefront per
-    // output channel for few columns, whole rows over LDS tiles for many
-    const int32_t images = static_cast<int32_t>(m / hw);
-    const bool few = spconv::rows_pay(plan->dev, images, hw);
-    const bool strip_rows = !few && spconv::strip_rows_pay(plan->dev, images, hw, image_bytes);
-    if (few) {
+    switch (choose_kernel(plan, plan->dev, n, hw, image_bytes)) {
+    case SPCONV_RUN_ROWS:
         he = spconv::launch_rows(plan->dev, static_cast<const float *>(x), static_cast<float *>(y),
                                  static_cast<int32_t>(m), static_cast<int32_t>(hw), static_cast<hipStream_t>(stream));
-    } else if (!plan->passes.empty()) {
+        break;
+    case SPCONV_RUN_PASSES:
         // channel-range passes in order: pass i reads X from its first channel
         for (size_t i = 0; i < plan->passes.size() && he == hipSuccess; ++i) {
             const int64_t skip = static_cast<int64_t>(plan->pass_c0[i]) * ihw * static_cast<int64_t>(e);
@@ -776,32 +795,63 @@ spconv_status spconv_run(spconv_plan plan, const void *x, void *y, int32_t n, in
                                      xel * static_cast<int64_t>(e) - skip, yel * static_cast<int64_t>(e), h, w,
                                      static_cast<int32_t>(ow), static_cast<hipStream_t>(stream));
         }
-    } else if (plan->dev.hkb > 0)
+        break;
+    case SPCONV_RUN_HALF:
         he = spconv::launch_half(plan->dev, x, y, static_cast<int32_t>(m), static_cast<int32_t>(hw),
                                  hw % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 8 == 0 &&
                                      reinterpret_cast<uintptr_t>(y) % 8 == 0,
                                  xel * static_cast<int64_t>(e), yel * static_cast<int64_t>(e),
                                  static_cast<hipStream_t>(stream));
-    else if (strip_rows)
+        break;
+    case SPCONV_RUN_LDS_ROWS:
         he = spconv::launch_strip_rows(plan->dev, static_cast<const float *>(x), static_cast<float *>(y),
                                        static_cast<int32_t>(m), static_cast<int32_t>(hw),
                                        xel * static_cast<int64_t>(e), yel * static_cast<int64_t>(e),
                                        static_cast<hipStream_t>(stream));
-    else if (outer)
+        break;
+    case SPCONV_RUN_OUTER:
         he = spconv::launch_outer(plan->dev, x, y, static_cast<int32_t>(m), static_cast<int32_t>(hw),
                                   hw % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
                                       reinterpret_cast<uintptr_t>(y) % 16 == 0,
                                   xel * static_cast<int64_t>(e), static_cast<hipStream_t>(stream));
-    else if (indexed)
+        break;
+    case SPCONV_RUN_INDEXED:
         he = spconv::launch_indexed(plan->dev, static_cast<const float *>(x), static_cast<float *>(y),
                                     static_cast<int32_t>(m), static_cast<int32_t>(hw), xel * static_cast<int64_t>(e),
                                     yel * static_cast<int64_t>(e), static_cast<hipStream_t>(stream));
-    else
+        break;
+    default:
         he = spconv::launch_spmm(plan->dev, x, y, static_cast<int32_t>(m), static_cast<int32_t>(hw), vec,
                                  xel * static_cast<int64_t>(e), yel * static_cast<int64_t>(e), h, w,
                                  static_cast<int32_t>(ow), static_cast<hipStream_t>(stream));
+    }
     if (he != hipSuccess)
         return hip_fail("kernel launch", he);
+    return SPCONV_OK;
+}
+
+spconv_status spconv_plan_run_kernel(spconv_plan plan, int32_t n, int32_t h, int32_t w, int32_t *kernel) {
+    g_err.clear();
+    if (!plan || !kernel)
+        return fail(SPCONV_E_ARG, "plan or kernel is NULL");
+    if (n < 0 || h < 0 || w < 0)
+        return fail(SPCONV_E_ARG, "n, h and w must be >= 0");
+    *kernel = SPCONV_RUN_NONE;
+    const spconv::PackedPlan &p = plan->host;
+    const int32_t s = p.dw_stride ? p.dw_stride : 1;
+    const int64_t hw = n && h && w ? static_cast<int64_t>((h - 1) / s + 1) * ((w - 1) / s + 1) : 0;
+    const int64_t ihw = static_cast<int64_t>(h) * w;
+    if (hw == 0)
+        return SPCONV_OK;
+    if (ihw > INT32_MAX || n * ihw > INT32_MAX)
+        return fail(SPCONV_E_SHAPE, "n * h * w must be below 2^31 columns");
+    spconv::DevicePlan d = plan->dev;
+    if (plan->host_only) {
+        d.num_cus = kHostOnlyCus;
+        d.indexed_min_cols = indexed_min_cols(p, d);
+        d.outer_min_cols = outer_min_cols(p, d);
+    }
+    *kernel = choose_kernel(plan, d, n, hw, std::max(ihw * p.cin, hw * p.cout) * (p.storage == 1 ? 2 : 4));
     return SPCONV_OK;
 }
 

@@ -357,7 +357,7 @@ __global__ void __launch_bounds__(1024) strip_rows_kernel(SArgs a) {
 // against 13.7, four 8.5 against 14.4, eight 13.4 against 14.9; 32 -> 64 @ 56 x
 // 56: one image 3.3 against 5.1, four 4.5 against 5.8, eight 6.2 against 6.2.
 bool rows_pay(const DevicePlan &p, int64_t images, int64_t hw) {
-    if (!p.trow_ptr || p.storage != 0 || hw < 4)
+    if (!p.rows || hw < 4)
         return false;
     const int64_t units = images * ((hw + 3) / 4);
     if (units > (int64_t(1) << 20))
@@ -388,7 +388,7 @@ bool rows_pay(const DevicePlan &p, int64_t images, int64_t hw) {
 // @ 28 x 28 16.8 against 14.3, and with 12 blocks, 128 -> 48, 50.3 against 41.2,
 // or 80% sparse 97.8 against 56.0).
 bool strip_rows_pay(const DevicePlan &p, int64_t images, int64_t hw, int64_t image_bytes) {
-    if (!p.glist || p.storage != 0 || hw < 4)
+    if (p.groups == 0 || hw < 4)
         return false;
     const int64_t units = (hw + 3) / 4, all = images * units;
     // the images of a tile must span less than 2^31 bytes

@@ -33,7 +33,7 @@ EXPORTED = ("spconv_plan_create", "spconv_run", "spconv_destroy", "spconv_last_e
             "spconv_global_avg_pool", "spconv_linear", "spconv_plan_create_blocked", "spconv_detect_blocks",
             "spconv_dense_to_bcsr_blocked", "spconv_plan_create_dense_blocked", "spconv_plan_unpack_indexed",
             "spconv_plan_check", "spconv_plan_set_wait_limit", "spconv_plan_create_static",
-            "spconv_plan_unpack_outer")
+            "spconv_plan_unpack_outer", "spconv_plan_run_kernel")
 
 
 class SpconvError(RuntimeError):
@@ -104,6 +104,8 @@ def load_library(path: Optional[str] = None):
     lib.spconv_options_init.argtypes = [ctypes.POINTER(spconv_options)]
     lib.spconv_plan_get_info.restype = i32
     lib.spconv_plan_get_info.argtypes = [vp, ctypes.POINTER(spconv_plan_info)]
+    lib.spconv_plan_run_kernel.restype = i32
+    lib.spconv_plan_run_kernel.argtypes = [vp, i32, i32, i32, ctypes.POINTER(i32)]
     lib.spconv_plan_unpack.restype = i32
     lib.spconv_plan_unpack.argtypes = [vp, vp, vp, vp, vp]
     lib.spconv_plan_unpack_interleaved.restype = i32
@@ -433,6 +435,16 @@ def spconv_plan_get_info(plan) -> dict:
     return info.as_dict()
 
 
+RUN_KERNELS = ("none", "strip", "direct", "indexed", "outer", "passes", "half", "rows", "lds rows")
+
+
+def spconv_plan_run_kernel(plan, n, h, w) -> str:
+    """The kernel that a run of n images of h x w takes (one of RUN_KERNELS)."""
+    k = ctypes.c_int32()
+    _check(load_library().spconv_plan_run_kernel(plan, int(n), int(h), int(w), ctypes.byref(k)))
+    return RUN_KERNELS[k.value]
+
+
 def spconv_plan_unpack(plan):
     """Return (row_ptr, col_idx, values, perm) rebuilt from the plan's packed host image."""
     info = spconv_plan_get_info(plan)
@@ -578,6 +590,10 @@ class Plan:
 
     def info(self) -> dict:
         return spconv_plan_get_info(self.handle)
+
+    def run_kernel(self, n, h, w) -> str:
+        """The kernel that run() takes for n images of h x w."""
+        return spconv_plan_run_kernel(self.handle, n, h, w)
 
     def run(self, x, y=None, stream=None):
         import torch

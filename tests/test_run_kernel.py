@@ -1,0 +1,80 @@
+"""Which kernel a run takes (spconv_plan_run_kernel), on host-only plans: no GPU.
+
+spconv_run launches what this call reports (one function decides for both), so
+these cases pin the rules: forced kernels are honoured at every size, and the
+automatic choice takes the kernels that the sizes and types ask for."""
+
+import ctypes
+
+import pytest
+
+import paper_1911_09723_amd as sp
+from paper_1911_09723_amd import Plan, spconv
+from synth import make_layer
+
+
+def run_kernel(layer, n, h, w, **options):
+    plan = Plan.from_layer(layer, host_only=1, **options)
+    try:
+        return plan.run_kernel(n, h, w)
+    finally:
+        plan.close()
+
+
+def layer_of(cin, cout, sparsity=0.9, **kw):
+    return make_layer(cin, cout, 1, 1, 1, sparsity, seed=cin + cout, with_x=False, **kw)
+
+
+@pytest.mark.parametrize("n,h,w", [(1, 14, 14), (256, 14, 14), (3, 7, 7), (5, 1, 3)])
+@pytest.mark.parametrize("kernel,name", [(1, "strip"), (2, "direct"), (3, "indexed"), (4, "outer")])
+def test_forced_kernels_run_at_every_size(kernel, name, n, h, w):
+    assert run_kernel(layer_of(64, 96), n, h, w, kernel=kernel) == name
+    assert run_kernel(layer_of(512, 512), n, h, w, kernel=kernel) == name
+
+
+# (cin, cout, keywords of the layer, n, h, w, kernel)
+AUTO = [
+    (512, 512, {}, 1, 14, 14, "rows"),            # few columns
+    (512, 512, {}, 256, 14, 14, "strip"),
+    (128, 128, {}, 64, 56, 56, "lds rows"),       # up to 160 input channels, many columns
+    (160, 960, {}, 128, 7, 7, "lds rows"),
+    (161, 960, {}, 128, 7, 7, "strip"),
+    (64, 128, {}, 64, 1, 3, "strip"),             # planes of fewer than 4 columns: no row kernel
+    (512, 512, {"block_rows": 4}, 256, 14, 14, "outer"),
+    (960, 160, {}, 128, 7, 7, "outer"),           # too wide for a strip
+    (1280, 320, {}, 128, 7, 7, "passes"),
+    (112, 672, {"block_rows": 4, "storage": "f16"}, 512, 14, 14, "half"),
+    (1217, 64, {"storage": "f16"}, 64, 14, 14, "direct"),
+    (8, 8, {}, 0, 14, 14, "none"),
+    (8, 8, {}, 1, 0, 14, "none"),
+]
+
+
+@pytest.mark.parametrize("cin,cout,kw,n,h,w,name", AUTO)
+def test_automatic_choice(cin, cout, kw, n, h, w, name):
+    assert run_kernel(layer_of(cin, cout, **kw), n, h, w) == name
+
+
+def test_depthwise_stage_counts_output_columns():
+    from synth import make_depthwise
+    layer = layer_of(32, 64)
+    kw, kb = make_depthwise(32, 5)
+    plan = Plan.fused(64, 32, 1, layer.row_ptr, layer.col_idx, layer.values, layer.bias, "relu", kw, kb, "relu", 2,
+                      host_only=1)
+    try:
+        assert plan.run_kernel(1, 15, 15) == "strip"
+    finally:
+        plan.close()
+
+
+def test_arguments():
+    lib = sp.load_library()
+    k = ctypes.c_int32(7)
+    plan = Plan.from_layer(layer_of(8, 8), host_only=1)
+    try:
+        assert lib.spconv_plan_run_kernel(None, 1, 1, 1, ctypes.byref(k)) == spconv.E_ARG
+        assert lib.spconv_plan_run_kernel(plan.handle, 1, 1, 1, None) == spconv.E_ARG
+        assert lib.spconv_plan_run_kernel(plan.handle, -1, 1, 1, ctypes.byref(k)) == spconv.E_ARG
+        assert lib.spconv_plan_run_kernel(plan.handle, 1 << 16, 1 << 10, 1 << 10, ctypes.byref(k)) == spconv.E_SHAPE
+    finally:
+        plan.close()
