@@ -783,7 +783,7 @@ Status build_plan(const Input &in_arg, const Options &opt, PackedPlan &p, std::s
         else
             lay_out(INT32_MAX);
     }
-    if (p.auto_kernel && opt.split)
+    if (p.auto_kernel && opt.split && opt.rows)
         build_rows(in, p.split_rows ? split_min : INT32_MAX, p);
     const int32_t nb = bundles_of(static_cast<int32_t>(ents.size()), NB);
     ents.resize(static_cast<size_t>(nb) * NB, Entry{-1, -1});

@@ -423,6 +423,7 @@ spconv_status create_plan(spconv_plan *out, const spconv::Input &in, const spcon
                                               "a depthwise stage, not in the static device array");
         }
         po.kernel = 0;  // the plan itself: the automatic choice (its image serves unpacking and info)
+        po.rows = auto_passes ? 1 : 0;  // passes asked for run at every size
     }
 
     spconv_plan_s *pl = new (std::nothrow) spconv_plan_s();

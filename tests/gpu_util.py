@@ -39,6 +39,15 @@ def gpu_run(layer, x=None, **options):
         plan.close()
 
 
+def assert_runs(layer, kernel, **options):
+    """The run of layer.x takes this kernel (one of spconv.RUN_KERNELS)."""
+    plan = Plan.from_layer(layer, **options)
+    try:
+        assert plan.run_kernel(layer.n, layer.h, layer.w) == kernel
+    finally:
+        plan.close()
+
+
 def note(msg: str):
     """Name the case on stdout before the GPU runs it (flushed)."""
     print(msg, flush=True)

@@ -10,7 +10,7 @@ import numpy as np
 import pytest
 
 from synth import make_layer
-from gpu_util import gpu_run, assert_parity, note, to_gpu
+from gpu_util import gpu_run, assert_parity, assert_runs, note, to_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -33,6 +33,7 @@ def test_channel_range_passes_match_oracle_and_direct_kernel(spec):
     cin, cout, h, w, n, act = spec
     layer = make_layer(cin, cout, h, w, n, 0.9, act=act, seed=cin + cout + n)
     note("passes %s" % (spec,))
+    assert_runs(layer, "passes", kernel=5)
     y5 = gpu_run(layer, kernel=5)
     assert_parity(layer, y5, what="passes %s" % (spec,))
     y2 = gpu_run(layer, kernel=2)
@@ -46,6 +47,7 @@ def test_channel_range_passes_unaligned_pointers():
     layer = make_layer(1024, 64, 7, 7, 4, 0.9, act="relu", seed=5)
     plan = Plan.from_layer(layer, kernel=5)
     try:
+        assert plan.run_kernel(4, 7, 7) == "passes"
         note("passes unaligned")
         xb = to_gpu(np.concatenate([np.zeros(1, np.float32), layer.x.ravel()]))
         yb = torch.full((4 * 64 * 49 + 1,), float("nan"), device="cuda:0")
@@ -61,12 +63,14 @@ def test_channel_range_passes_unaligned_pointers():
 
 def test_automatic_choice_runs_passes_beyond_the_lockstep_limit():
     """1300 input channels: the automatic choice plans three ranges (512, 512,
-    276) and gives the direct-load kernel's bits."""
+    276), runs them on all but short runs and gives the direct-load kernel's
+    bits."""
     from paper_1911_09723_amd import Plan
-    layer = make_layer(1300, 40, 7, 7, 2, 0.9, act="relu6", seed=13)
+    layer = make_layer(1300, 40, 14, 14, 128, 0.9, act="relu6", seed=13)
     plan = Plan.from_layer(layer)
     try:
         assert plan.info()["channel_passes"] == 3
+        assert plan.run_kernel(128, 14, 14) == "passes"
     finally:
         plan.close()
     note("passes automatic 1300")
@@ -91,6 +95,7 @@ def test_rows_empty_in_some_ranges_or_everywhere():
     layer.col_idx = np.array(ci, np.int32)
     layer.values = np.array(va, np.float32)
     note("passes empty ranges")
+    assert_runs(layer, "passes", kernel=5)
     y5 = gpu_run(layer, kernel=5)
     assert_parity(layer, y5, what="passes empty ranges")
     assert np.array_equal(y5.view(np.uint32), gpu_run(layer, kernel=2).view(np.uint32))

@@ -32,6 +32,12 @@ def test_forced_kernels_run_at_every_size(kernel, name, n, h, w):
     assert run_kernel(layer_of(512, 512), n, h, w, kernel=kernel) == name
 
 
+@pytest.mark.parametrize("cin,cout", [(600, 64), (1024, 96), (1030, 48), (1280, 320), (1300, 40)])
+@pytest.mark.parametrize("n,h,w", [(1, 7, 7), (1, 8, 8), (3, 5, 5), (64, 7, 7)])
+def test_forced_passes_run_at_every_size(cin, cout, n, h, w):
+    assert run_kernel(layer_of(cin, cout), n, h, w, kernel=5) == "passes"
+
+
 # (cin, cout, keywords of the layer, n, h, w, kernel)
 AUTO = [
     (512, 512, {}, 1, 14, 14, "rows"),            # few columns
