@@ -39,11 +39,11 @@ def gpu_run(layer, x=None, **options):
         plan.close()
 
 
-def assert_runs(layer, kernel, **options):
+def assert_runs(layer, name, **options):
     """The run of layer.x takes this kernel (one of spconv.RUN_KERNELS)."""
     plan = Plan.from_layer(layer, **options)
     try:
-        assert plan.run_kernel(layer.n, layer.h, layer.w) == kernel
+        assert plan.run_kernel(layer.n, layer.h, layer.w) == name
     finally:
         plan.close()
 
