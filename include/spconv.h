@@ -278,12 +278,19 @@ typedef struct {
     int32_t struct_size; /* sizeof(spconv_options) */
     int32_t reorder;     /* 1 (default): process rows in descending nonzero order; 0: natural order */
     int32_t host_only;   /* 1: plan on the host only, no device memory; spconv_run refuses it */
-    int32_t kernel;      /* 0 = choose automatically: the LDS-strip or direct-load kernel, or, for
+    int32_t kernel;      /* 0 = choose automatically at each run (spconv_plan_run_kernel says
+                            which): fp16, the half kernel up to 1216 input channels and 16 MiB
+                            of dense weights; fp32, a row kernel for runs of few columns, or of
+                            up to 160 input channels over LDS tiles, where it measured faster;
+                            else the LDS-strip or direct-load kernel, or, for
                             runs with enough columns on layers where it measured faster, the
                             register-indexed kernel (spconv_plan_info.indexed_min_cols) or the
                             outer-product kernel (spconv_plan_info.outer_min_cols); fp32
                             unstructured inputs of more than 1264 channels take channel-range
-                            passes (5);
+                            passes (5).  The half and the row kernels have one layout: a plan
+                            with reorder = 0 or any of the fields below set, one with a
+                            depthwise stage, and a static plan whose image is too large with
+                            their arrays go without them;
                             1 = LDS-strip kernel (SPCONV_E_UNSUPPORTED when the strip of cin
                             channels does not fit in LDS); 2 = direct-load kernel; 3 =
                             register-indexed kernel (SPCONV_E_UNSUPPORTED for fp16 storage or a

@@ -700,7 +700,7 @@ Status build_plan(const Input &in_arg, const Options &opt, PackedPlan &p, std::s
         p.rlane_cols = opt.lane_cols;
     }
     p.auto_kernel = opt.kernel == 0;
-    if (p.auto_kernel)
+    if (p.auto_kernel && opt.half_rows)
         build_half(in, p);
     if (outer_supported(in) && (opt.kernel == 0 || opt.kernel == 4)) {
         build_outer(in, p);
@@ -783,7 +783,7 @@ Status build_plan(const Input &in_arg, const Options &opt, PackedPlan &p, std::s
         else
             lay_out(INT32_MAX);
     }
-    if (p.auto_kernel && opt.split && opt.rows)
+    if (p.auto_kernel && opt.split && opt.half_rows)
         build_rows(in, p.split_rows ? split_min : INT32_MAX, p);
     const int32_t nb = bundles_of(static_cast<int32_t>(ents.size()), NB);
     ents.resize(static_cast<size_t>(nb) * NB, Entry{-1, -1});

@@ -285,7 +285,7 @@ struct Options {
     int32_t lane_cols = 0;    // register-indexed kernel: 0 automatic, else 1 .. 6 columns per lane
     int32_t split = 1;        // heavy rows may be packed as two pieces (off for channel-range passes,
                               // whose rows must be summed in one ascending pass)
-    int32_t rows = 1;         // the automatic choice may take the row kernels
+    int32_t half_rows = 1;    // the automatic choice may take the half and the row kernels
 };
 
 // One lane group of a bundle as the row table describes it (group_row).

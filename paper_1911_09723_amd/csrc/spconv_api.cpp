@@ -416,6 +416,10 @@ spconv_status create_plan(spconv_plan *out, const spconv::Input &in, const spcon
     const bool auto_passes = o.kernel == 0 && in.cin > spconv::kOuterMaxCin16 && in.block_rows == 1 &&
                              in.block_cols <= 1 && in.storage == 0 && !in.dw_stride && !use_static && xc == 0;
     const bool passes = o.kernel == kKernelPasses || auto_passes;
+    // Passes asked for run at every size.  The half and the row kernels have one
+    // layout, so a caller who picks the layout gets the kernels that have others.
+    po.half_rows = o.kernel != kKernelPasses && o.reorder && !o.group_lanes && !o.waves && !o.pipe_sets &&
+                   !o.regions && !o.lane_cols;
     if (passes) {
         if (in.block_rows != 1 || in.block_cols > 1 || in.storage != 0 || in.dw_stride || use_static) {
             *out = nullptr;
@@ -423,7 +427,6 @@ spconv_status create_plan(spconv_plan *out, const spconv::Input &in, const spcon
                                               "a depthwise stage, not in the static device array");
         }
         po.kernel = 0;  // the plan itself: the automatic choice (its image serves unpacking and info)
-        po.rows = auto_passes ? 1 : 0;  // passes asked for run at every size
     }
 
     spconv_plan_s *pl = new (std::nothrow) spconv_plan_s();

@@ -61,6 +61,20 @@ def test_automatic_choice(cin, cout, kw, n, h, w, name):
     assert run_kernel(layer_of(cin, cout, **kw), n, h, w) == name
 
 
+@pytest.mark.parametrize("option", ["group_lanes", "waves", "pipe_sets", "regions", "lane_cols", "reorder"])
+def test_layout_options_keep_the_kernels_that_they_lay_out(option):
+    """The half and the row kernels have no lane groups, bundles or strip
+    parts: a caller who sets one of these gets a kernel that uses it."""
+    value = {"group_lanes": 8, "waves": 5, "pipe_sets": 1, "regions": 2, "lane_cols": 4, "reorder": 0}[option]
+    assert run_kernel(layer_of(256, 256), 4, 14, 14) == "rows"
+    assert run_kernel(layer_of(256, 256), 4, 14, 14, **{option: value}) == "strip"
+    assert run_kernel(layer_of(64, 96), 64, 28, 28) == "lds rows"
+    assert run_kernel(layer_of(64, 96), 64, 28, 28, **{option: value}) in ("strip", "indexed")
+    f16 = layer_of(64, 96, storage="f16")
+    assert run_kernel(f16, 64, 28, 28) == "half"
+    assert run_kernel(f16, 64, 28, 28, **{option: value}) == "strip"
+
+
 def test_depthwise_stage_counts_output_columns():
     from synth import make_depthwise
     layer = layer_of(32, 64)
