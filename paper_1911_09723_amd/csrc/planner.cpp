@@ -784,7 +784,10 @@ Status build_plan(const Input &in_arg, const Options &opt, PackedPlan &p, std::s
             lay_out(INT32_MAX);
     }
     if (p.auto_kernel && opt.split && opt.half_rows)
-        build_rows(in, p.split_rows ? split_min : INT32_MAX, p);
+        // (too wide for a strip, the run's size decides between a row kernel and
+        // the lockstep kernel or passes, which sum a row in one chain: so does
+        // the row kernel, and an image's bits do not depend on its batch)
+        build_rows(in, p.split_rows && p.kernel == KERNEL_STRIP ? split_min : INT32_MAX, p);
     const int32_t nb = bundles_of(static_cast<int32_t>(ents.size()), NB);
     ents.resize(static_cast<size_t>(nb) * NB, Entry{-1, -1});
     std::vector<int32_t> bsteps(nb, 0);

@@ -18,7 +18,7 @@ import numpy as np
 import pytest
 
 from synth import make_layer, densify
-from gpu_util import gpu_run, assert_parity, note, to_gpu, device
+from gpu_util import gpu_run, assert_parity, assert_runs, note, to_gpu, device
 
 pytestmark = pytest.mark.gpu
 
@@ -167,3 +167,19 @@ def test_split_rows_keep_the_strip_kernels_sums(spec):
     y = gpu_run(layer)
     assert_parity(layer, y, what=str(spec))
     assert np.array_equal(y.view(np.uint32), gpu_run(layer, kernel=1).view(np.uint32))
+
+
+@pytest.mark.parametrize("cin,cout,s,n,name", [(640, 96, 0.95, 256, "outer"), (1264, 40, 0.95, 512, "outer"),
+                                               (1400, 96, 0.98, 512, "passes")])
+def test_wide_heavy_tailed_rows_do_not_depend_on_the_batch(cin, cout, s, n, name):
+    """Heavy-tailed layers too wide for an LDS strip: a short run takes the row
+    kernel, a long one a kernel that sums every row in one chain.  An image
+    alone gives the bits that it gives among others."""
+    layer = make_layer(cin, cout, 7, 7, n, s, pattern="beta", act="none", seed=cin)
+    note("rows wide %d -> %d" % (cin, cout))
+    assert_runs(layer, name)
+    y = gpu_run(layer)
+    assert_parity(layer, y, what="%d -> %d" % (cin, cout))
+    layer.x, layer.n = layer.x[:2], 2
+    assert_runs(layer, "rows")
+    assert np.array_equal(gpu_run(layer).view(np.uint32), y[:2].view(np.uint32))
