@@ -345,7 +345,7 @@ spconv_run_kernel choose_kernel(const spconv_plan_s *pl, const spconv::DevicePla
         return SPCONV_RUN_ROWS;
     if (!pl->passes.empty())
         return SPCONV_RUN_PASSES;
-    if (d.hkb > 0)
+    if (spconv::half_runs(d, images, hw, image_bytes))
         return SPCONV_RUN_HALF;
     if (spconv::strip_rows_pay(d, images, hw, image_bytes))
         return SPCONV_RUN_LDS_ROWS;

@@ -61,6 +61,7 @@ using Rsrc = __amdgpu_buffer_rsrc_t;
 // An offset past every buffer resource: loads return zeros, stores are dropped.
 constexpr int32_t kOutOfRange = static_cast<int32_t>(0x80000000u);
 constexpr int64_t kMaxRecords = 0x7ffffff0;
+constexpr int32_t kXcds = 8;
 
 __device__ __forceinline__ Rsrc make_rsrc(const void *p, int64_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), static_cast<short>(0),
@@ -417,6 +418,80 @@ hipError_t prepare_half(const DevicePlan &p) {
     return hipSuccess;
 }
 
+namespace {
+
+// How a run is cut into tiles and workgroups.
+struct HalfShape {
+    int nh;                            // parts at a time
+    int32_t units, chunks, ipt, tpi, tunits, parts, rgroups, rsplit, waves, lds;
+    int64_t tiles;
+    int64_t grid;
+};
+
+HalfShape half_shape(const DevicePlan &p, int64_t images, int64_t hw, int64_t image_bytes) {
+    HalfShape s;
+    const int32_t kb = p.hkb;
+    s.units = static_cast<int32_t>((hw + 3) / 4);
+    const int32_t cus = std::max(p.num_cus, 1);
+    // Parts at a time and per tile.  Whole planes of up to 64 units are taken
+    // four parts at a time, larger ones by 4 wavefronts with four parts each
+    // where that fits in LDS (40 -> 240 @ 28 x 28, batch 512: 52 us against 70
+    // in four pieces); two parts otherwise, one where LDS holds no more or the
+    // run is too short to fill the card (few tiles, or few rows for a
+    // workgroup's wavefronts to share).
+    const int32_t row_tiles16 = (p.cout + 15) / 16;
+    const int64_t units16 = images * ((s.units + 15) / 16);  // parts of the whole run
+    s.nh = kb > 19 ? 1 : s.units > 32 && kb <= kHalfRing - 1 ? 4 : 2;
+    if (row_tiles16 <= 4 && s.nh == 4 && kb > 1)
+        s.nh = 2;
+    if (units16 < 4 * cus && s.nh > 1)
+        s.nh = units16 < cus ? 1 : 2;
+    s.chunks = 1;
+    if (s.nh == 4 && s.units > 64 && kb <= 2)
+        s.chunks = s.units > 128 ? 4 : 2;
+    const int32_t rt = row_tiles(kb);
+    s.rgroups = (p.cout + 16 * rt - 1) / (16 * rt);
+    const int32_t most = 16 * s.nh * s.chunks;  // units of a tile, at most
+    if (s.units > most) {
+        s.ipt = 1;
+        s.tpi = (s.units + most - 1) / most;
+        s.tunits = (s.units + s.tpi - 1) / s.tpi;
+    } else {
+        // (the images of a tile must span less than 2^31 bytes)
+        s.tpi = 1;
+        s.ipt = static_cast<int32_t>(std::min<int64_t>(most / s.units,
+                                                       std::max<int64_t>(1, (int64_t(1) << 30) / image_bytes)));
+        s.tunits = s.ipt * s.units;
+    }
+    s.parts = ((s.tunits + 15) / 16 + s.nh - 1) / s.nh * s.nh;
+    s.tiles = s.tpi > 1 ? images * s.tpi : (images + s.ipt - 1) / s.ipt;
+    s.lds = half_lds_bytes(kb, s.parts);
+    // wavefronts: 16 a compute unit, in one workgroup where LDS or the number
+    // of tiles leaves no second one (192 -> 1152 @ 7 x 7, batch 512, 256
+    // tiles: 34 us against 44 with 8); fewer in short runs, whose tiles are
+    // shared by row groups, and for few rows
+    s.waves = 2 * s.tiles < cus                                         ? (s.lds > kMaxLdsBytes / 2 ? 8 : 2)
+              : s.lds > kMaxLdsBytes / 2 || s.tiles <= 3 * cus / 2 ? 16
+                                                                   : 8;
+    if (row_tiles16 <= 4 && kb > 1)
+        s.waves = std::min(s.waves, 4);
+    s.waves = std::max(s.waves, s.chunks);
+    const int32_t rows = s.waves / s.chunks;  // row groups a workgroup works on at a time
+    s.rsplit = static_cast<int32_t>(
+        std::max<int64_t>(1, std::min<int64_t>((s.rgroups + rows - 1) / rows, 2 * cus / (2 * s.tiles))));
+    s.grid = (s.tiles * s.rsplit + kXcds - 1) / kXcds * kXcds;
+    return s;
+}
+
+}  // namespace
+
+bool half_runs(const DevicePlan &p, int64_t images, int64_t hw, int64_t image_bytes) {
+    if (p.hkb == 0)
+        return false;
+    const HalfShape s = half_shape(p, images, hw, image_bytes);
+    return s.grid * 64 * s.waves < int64_t(1) << 32;
+}
+
 hipError_t launch_half(const DevicePlan &p, const void *x, void *y, int32_t m, int32_t hw, int32_t vec,
                        int64_t x_bytes, int64_t y_bytes, hipStream_t stream) {
     HArgs a;
@@ -431,62 +506,23 @@ hipError_t launch_half(const DevicePlan &p, const void *x, void *y, int32_t m, i
     a.hw = hw;
     a.images = m / hw;
     a.kb = p.hkb;
-    a.units = (hw + 3) / 4;
     a.x_bytes = x_bytes;
     a.y_bytes = y_bytes;
     a.lo = p.act == 0 ? -__builtin_huge_valf() : 0.0f;
     a.hi = p.act == 2 ? 6.0f : __builtin_huge_valf();
-    const int32_t cus = std::max(p.num_cus, 1);
-    // Parts at a time and per tile.  Whole planes of up to 64 units are taken
-    // four parts at a time, larger ones by 4 wavefronts with four parts each
-    // where that fits in LDS (40 -> 240 @ 28 x 28, batch 512: 52 us against 70
-    // in four pieces); two parts otherwise, one where LDS holds no more or the
-    // run is too short to fill the card (few tiles, or few rows for a
-    // workgroup's wavefronts to share).
-    const int32_t row_tiles16 = (p.cout + 15) / 16;
-    const int64_t units16 = static_cast<int64_t>(a.images) * ((a.units + 15) / 16);  // parts of the whole run
-    int nh = a.kb > 19 ? 1 : a.units > 32 && a.kb <= kHalfRing - 1 ? 4 : 2;
-    if (row_tiles16 <= 4 && nh == 4 && a.kb > 1)
-        nh = 2;
-    if (units16 < 4 * cus && nh > 1)
-        nh = units16 < cus ? 1 : 2;
-    a.chunks = 1;
-    if (nh == 4 && a.units > 64 && a.kb <= 2)
-        a.chunks = a.units > 128 ? 4 : 2;
-    const int32_t rt = row_tiles(a.kb);
-    a.rgroups = (p.cout + 16 * rt - 1) / (16 * rt);
-    const int32_t most = 16 * nh * a.chunks;  // units of a tile, at most
-    if (a.units > most) {
-        a.ipt = 1;
-        a.tpi = (a.units + most - 1) / most;
-        a.tunits = (a.units + a.tpi - 1) / a.tpi;
-    } else {
-        // (the images of a tile must span less than 2^31 bytes)
-        const int64_t image_bytes = std::max(x_bytes, y_bytes) / a.images;
-        a.tpi = 1;
-        a.ipt = static_cast<int32_t>(std::min<int64_t>(most / a.units,
-                                                       std::max<int64_t>(1, (int64_t(1) << 30) / image_bytes)));
-        a.tunits = a.ipt * a.units;
-    }
-    a.parts = ((a.tunits + 15) / 16 + nh - 1) / nh * nh;
-    a.tiles = a.tpi > 1 ? a.images * a.tpi : (a.images + a.ipt - 1) / a.ipt;
-    const int32_t lds = half_lds_bytes(a.kb, a.parts);
-    // wavefronts: 16 a compute unit, in one workgroup where LDS or the number
-    // of tiles leaves no second one (192 -> 1152 @ 7 x 7, batch 512, 256
-    // tiles: 34 us against 44 with 8); fewer in short runs, whose tiles are
-    // shared by row groups, and for few rows
-    int32_t waves = 2 * static_cast<int64_t>(a.tiles) < cus             ? (lds > kMaxLdsBytes / 2 ? 8 : 2)
-                    : lds > kMaxLdsBytes / 2 || a.tiles <= 3 * cus / 2 ? 16
-                                                                        : 8;
-    if (row_tiles16 <= 4 && a.kb > 1)
-        waves = std::min(waves, 4);
-    waves = std::max(waves, a.chunks);
-    const int32_t rows = waves / a.chunks;  // row groups a workgroup works on at a time
-    a.rsplit = std::max<int32_t>(1, std::min<int32_t>((a.rgroups + rows - 1) / rows, 2 * cus / (2 * a.tiles)));
-    a.nxcd = 8;
-    const int64_t items = static_cast<int64_t>(a.tiles) * a.rsplit;
-    const int64_t grid = (items + a.nxcd - 1) / a.nxcd * a.nxcd;
-    hipLaunchKernelGGL(pick(vec != 0, nh, a.kb), dim3(static_cast<unsigned>(grid)), dim3(64 * waves), lds, stream, a);
+    const HalfShape s = half_shape(p, a.images, hw, std::max(x_bytes, y_bytes) / a.images);
+    a.rgroups = s.rgroups;
+    a.units = s.units;
+    a.tunits = s.tunits;
+    a.tiles = static_cast<int32_t>(s.tiles);
+    a.ipt = s.ipt;
+    a.tpi = s.tpi;
+    a.parts = s.parts;
+    a.chunks = s.chunks;
+    a.rsplit = s.rsplit;
+    a.nxcd = kXcds;
+    hipLaunchKernelGGL(pick(vec != 0, s.nh, a.kb), dim3(static_cast<unsigned>(s.grid)), dim3(64 * s.waves), s.lds,
+                       stream, a);
     return hipGetLastError();
 }
 

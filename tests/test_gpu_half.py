@@ -73,6 +73,30 @@ def test_half_alignment_and_batch_do_not_change_bits(hw):
         plan.close()
 
 
+def test_half_longest_runs_take_another_kernel():
+    """2^28 + 5 images of one column: more workgroups than one launch takes."""
+    import torch
+    from paper_1911_09723_amd import Plan
+    from synth import densify
+    layer = make_layer(8, 8, 1, 1, 1, 0.5, storage="f16", act="none", seed=4, with_x=False)
+    n = (1 << 28) + 5
+    note("half longest run")
+    plan = Plan.from_layer(layer)
+    try:
+        assert plan.run_kernel(n, 1, 1) == "strip"
+        x = torch.randn((n, 8, 1, 1), device=device(), dtype=torch.float16)
+        y = plan.run(x)
+        w = to_gpu(densify(8, 8, 1, layer.row_ptr, layer.col_idx, layer.values).astype(np.float32))
+        b = to_gpu(layer.bias)
+        for i in range(0, n, 1 << 26):
+            ref = x[i:i + (1 << 26)].view(-1, 8).float() @ w.T + b
+            # one rounding to fp16 and fp32 sums of 8 terms
+            assert torch.all((y[i:i + (1 << 26)].view(-1, 8).float() - ref).abs() <= 1e-3 * ref.abs() + 2e-5)
+    finally:
+        plan.close()
+        torch.cuda.empty_cache()
+
+
 # output channels one to three past a row tile, and second row tiles wholly past
 # the last channel (two tiles a group, inputs of more than 320 channels)
 @pytest.mark.parametrize("cin,cout", [(32, 33), (32, 18), (96, 3), (300, 17), (352, 40), (352, 33), (640, 16)])

@@ -75,6 +75,16 @@ def test_layout_options_keep_the_kernels_that_they_lay_out(option):
     assert run_kernel(f16, 64, 28, 28, **{option: value}) == "strip"
 
 
+def test_half_kernel_only_where_its_workgroups_fit_one_launch():
+    """A launch has fewer than 2^32 threads; the half kernel's workgroups take
+    one tile each, so the longest runs take the kernel that loops over tiles."""
+    layer = layer_of(8, 8, 0.5, storage="f16")
+    assert run_kernel(layer, 1 << 27, 1, 1) == "half"
+    assert run_kernel(layer, 1 << 30, 1, 1) == "strip"
+    assert run_kernel(layer, 40 << 20, 7, 7) == "strip"
+    assert run_kernel(layer_of(8, 8, 0.5, storage="f16", block_rows=4), 1 << 30, 1, 1) in ("strip", "outer")
+
+
 def test_depthwise_stage_counts_output_columns():
     from synth import make_depthwise
     layer = layer_of(32, 64)
