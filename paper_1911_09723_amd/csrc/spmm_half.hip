@@ -37,8 +37,9 @@
 //
 // A dense product reads X where the sparse one does not, and 0 * inf is NaN.
 // Staging therefore checks every value: a workgroup that saw an infinity or a
-// NaN sums each of its outputs over the stored weights only, in ascending
-// channel, from the same LDS copy.
+// NaN sums the columns that hold one again, over the stored weights only, in
+// ascending channel, from the same LDS copy.  (Columns do not mix in the
+// products: the others keep their bits, whatever shares their tile.)
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -89,9 +90,10 @@ struct HArgs {
 };
 
 // A unit's columns: element offsets of the first one in channel 0 of X and of
-// Y from the tile's first image, and how many there are (0: none).
+// Y from the tile's first image, how many there are (0: none), and a bit for
+// each that holds an infinity or a NaN (after the products, where there are any).
 struct Unit {
-    int32_t xo, yo, k, pad;
+    int32_t xo, yo, k, mask;
 };
 
 __device__ __forceinline__ uint64_t load8(const _Float16 *p) {
@@ -239,32 +241,9 @@ __global__ void __launch_bounds__(1024) half_kernel(HArgs a) {
 
     const int64_t ybase = static_cast<int64_t>(n0) * a.cout * a.hw;
 
-    if (*bad) {
-        // the stored weights only: an infinity or a NaN must not reach the
-        // rows that do not read its channel
-        for (; rg < a.rgroups; rg += stride)
-            for (int32_t o = 64 * chunk + lane; o < 16 * RT * 64 * a.parts; o += 64 * a.chunks) {
-                const int32_t row = 16 * RT * rg + o / (64 * a.parts), c = o % (64 * a.parts);
-                const Unit u = tab[c >> 2];
-                if (row >= a.cout || (c & 3) >= u.k)
-                    continue;
-                const unsigned char *src = lds + ((c >> 6) * a.kb * 4 + (c & 3)) * 1024 + ((c & 63) >> 2) * 16;
-                float s = 0.0f;
-                for (int32_t t = a.row_ptr[row]; t < a.row_ptr[row + 1]; ++t) {
-                    const u2 en = a.ent[t];
-                    const int32_t ch = static_cast<int32_t>(en.x);
-                    const _Float16 xv = *reinterpret_cast<const _Float16 *>(src + (ch >> 5) * 4096 +
-                                                                            ((ch >> 3) & 3) * 256 + (ch & 7) * 2);
-                    s = __builtin_fmaf(__uint_as_float(en.y), static_cast<float>(xv), s);
-                }
-                a.y[ybase + u.yo + (c & 3) + static_cast<int64_t>(row) * a.hw] =
-                    static_cast<_Float16>(fminf(fmaxf(s + a.bias[row], a.lo), a.hi));
-            }
-        return;
-    }
-
     // ---- row groups ----
-    if (rg >= a.rgroups)
+    const int32_t redo = __builtin_amdgcn_readfirstlane(*bad);
+    if (rg >= a.rgroups && !redo)
         return;
     const Rsrc ry = make_rsrc(a.y + ybase, a.y_bytes - 2 * ybase);
     if constexpr (!kEarly)
@@ -364,6 +343,49 @@ __global__ void __launch_bounds__(1024) half_kernel(HArgs a) {
         }
         wp = wn;
     }
+
+    if (!redo)
+        return;
+    // The columns with an infinity or a NaN once more, over the stored weights
+    // only: neither may reach the rows that do not read its channel.
+    const int32_t columns = 64 * a.parts;
+    // (the lane and the shares anew: kept through the products they cost registers there)
+    const int32_t l = static_cast<int32_t>(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)));
+    int32_t wv = wave;
+    asm("" : "+s"(wv));
+    auto column = [&](int32_t c) { return lds + ((c >> 6) * a.kb * 4 + (c & 3)) * 1024 + ((c & 63) >> 2) * 16; };
+    for (int32_t c = 64 * wv + l; c < columns; c += 64 * waves) {
+        const unsigned char *src = column(c);
+        bool finite = true;
+        for (int32_t k = 0; k < 4 * a.kb; ++k) {  // 8 channels each
+            const u4 v = *reinterpret_cast<const u4 *>(src + (k >> 2) * 4096 + (k & 3) * 256);
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+                finite = finite && (v[w] & 0x7c00u) != 0x7c00u && (v[w] & 0x7c000000u) != 0x7c000000u;
+        }
+        if (!finite)
+            atomicOr(&tab[c >> 2].mask, 1 << (c & 3));
+    }
+    __threadfence();  // the products' results are written before these
+    __syncthreads();
+    for (rg = rs * (waves / a.chunks) + wv / a.chunks; rg < a.rgroups; rg += stride)
+        for (int32_t o = 64 * (wv % a.chunks) + l; o < 16 * RT * columns; o += 64 * a.chunks) {
+            const int32_t row = 16 * RT * rg + o / columns, c = o % columns;
+            const Unit u = tab[c >> 2];
+            if (row >= a.cout || (c & 3) >= u.k || !(u.mask >> (c & 3) & 1))
+                continue;
+            const unsigned char *src = column(c);
+            float s = 0.0f;
+            for (int32_t t = a.row_ptr[row]; t < a.row_ptr[row + 1]; ++t) {
+                const u2 en = a.ent[t];
+                const int32_t ch = static_cast<int32_t>(en.x);
+                const _Float16 xv =
+                    *reinterpret_cast<const _Float16 *>(src + (ch >> 5) * 4096 + ((ch >> 3) & 3) * 256 + (ch & 7) * 2);
+                s = __builtin_fmaf(__uint_as_float(en.y), static_cast<float>(xv), s);
+            }
+            a.y[ybase + u.yo + (c & 3) + static_cast<int64_t>(row) * a.hw] =
+                static_cast<_Float16>(fminf(fmaxf(s + a.bias[row], a.lo), a.hi));
+        }
 }
 
 typedef void (*HKernel)(HArgs);

@@ -15,7 +15,7 @@ import numpy as np
 import pytest
 
 from synth import make_layer, densify
-from gpu_util import gpu_run, assert_parity, note, to_gpu, device
+from gpu_util import gpu_run, assert_parity, assert_runs, note, to_gpu, device
 
 pytestmark = pytest.mark.gpu
 
@@ -95,6 +95,29 @@ def test_half_longest_runs_take_another_kernel():
     finally:
         plan.close()
         torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("spec", [(70, 45, 8, 8, 5), (70, 45, 7, 7, 9), (70, 45, 1, 3, 30), (40, 96, 28, 28, 70),
+                                  (96, 160, 13, 13, 400), (400, 80, 6, 6, 9), (128, 640, 4, 4, 3)],
+                         ids=lambda s: "%d-%d-%dx%d-n%d" % s)
+def test_half_non_finite_columns_leave_the_others_alone(spec):
+    """The same bits in every column without an infinity or a NaN, of the same
+    image and of the others in its tile."""
+    cin, cout, h, w, n = spec
+    layer = make_layer(cin, cout, h, w, n, 0.8, storage="f16", act="none", seed=cin + n)
+    note("half columns %s" % (spec,))
+    assert_runs(layer, "half")
+    y = gpu_run(layer)
+    x = layer.x.copy()
+    x[0, 3, 0, 0] = np.inf
+    x[n // 2, cin - 1, h - 1, w - 1] = np.nan
+    x[n // 2, 5, h // 2, w // 2] = -np.inf
+    finite = np.isfinite(x).all(axis=1)[:, None]
+    assert int((~finite).sum()) == 3
+    y2 = gpu_run(layer, x=x)
+    same = y.view(np.uint16) == y2.view(np.uint16)
+    assert (same | ~finite).all()
+    assert not same.all()
 
 
 # output channels one to three past a row tile, and second row tiles wholly past
