@@ -468,8 +468,9 @@ SPCONV_API spconv_status spconv_plan_unpack(spconv_plan plan, int32_t *row_ptr, 
  * The same reconstruction from the interleaved weight streams the pipelined
  * LDS-strip kernel reads (row_ptr, col_idx, values as above, each may be
  * NULL), walking them with the kernel's own bookkeeping: per step, the
- * accumulator set and last-step bits pick the bundle, and every strip channel
- * read must fall between the need and release events of its strip part.
+ * accumulator set and last-step bits pick the bundle, every strip channel
+ * read must fall between the need and release events of its strip part, and
+ * every wavefront must need each part before it releases it.
  * Host only.  SPCONV_E_FORMAT (message set) when the streams are inconsistent
  * or the plan has none (direct-load kernel, depthwise stage).
  */

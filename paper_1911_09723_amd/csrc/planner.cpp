@@ -497,6 +497,9 @@ void build_interleaved(PackedPlan &p) {
         }
         const int64_t len = static_cast<int64_t>(src.size());
         std::vector<int64_t> need(kMaxRegions, INT64_MAX), rel(kMaxRegions, -1);
+        // a region that the wave never reads: the step of its first read in a
+        // later region (which lands no sooner), or its last step
+        std::vector<int64_t> pass(kMaxRegions, len - 1);
         for (int64_t i = 0; i < len; ++i) {
             const int64_t d = ws0 + i;
             std::copy(p.idx.begin() + src[i] * rec, p.idx.begin() + (src[i] + 1) * rec, p.pidx.begin() + d * rec);
@@ -507,6 +510,8 @@ void build_interleaved(PackedPlan &p) {
                 if (m >> q & 1u) {
                     need[q] = std::min(need[q], i);
                     rel[q] = i;
+                } else if (m >> q > 1u) {
+                    pass[q] = std::min(pass[q], i);
                 }
         }
         const int64_t words = (len + kSelSteps - 1) / kSelSteps;
@@ -517,9 +522,13 @@ void build_interleaved(PackedPlan &p) {
         p.sel_ptr[w + 1] = static_cast<int32_t>(p.psel.size());
         std::vector<int32_t> ne, re;
         for (int32_t q = 0; q < p.regions; ++q) {
-            if (need[q] != INT64_MAX)
-                ne.push_back(static_cast<int32_t>(need[q] << 4 | q));
-            re.push_back(static_cast<int32_t>((rel[q] < 0 ? 0 : rel[q]) << 4 | q));
+            // the wave waits for every region that it counts as free: one that
+            // counted without waiting would run ahead into later tiles, and its
+            // counts stand in the sum for wavefronts that still read the region
+            if (rel[q] < 0)
+                need[q] = rel[q] = pass[q];
+            ne.push_back(static_cast<int32_t>(need[q] << 4 | q));
+            re.push_back(static_cast<int32_t>(rel[q] << 4 | q));
         }
         std::sort(ne.begin(), ne.end());
         std::sort(re.begin(), re.end());
@@ -1025,6 +1034,9 @@ Status unpack_interleaved(const PackedPlan &p, int32_t *row_ptr, int32_t *col_id
             if (r != INT32_MAX)
                 hi[r & 15] = r >> 4;
         }
+        for (int32_t q = 0; q < p.regions; ++q)
+            if (hi[q] < 0 || lo[q] > hi[q])
+                return bad("a wavefront releases a strip part that it did not wait for");
         std::vector<int32_t> bset(S), cnt(S, 0);
         for (int32_t i = 0; i < S; ++i)
             bset[i] = b0 + i;

@@ -62,11 +62,11 @@
 // that order.  Per wave:
 //   psel[sel_ptr[w] + i / 16] bits 2*(i % 16), +1   set of the wave's i-th step,
 //                    and whether it is its bundle's last step
-//   wave_ev[8*w + 0 .. 3]   (pos << 4) | region for each region the wave reads,
-//                    sorted by pos: the first step that reads it ("need")
-//   wave_ev[8*w + 4 .. 7]   the same for the last step that reads it
-//                    ("release"; step 0 for a region it never reads)
-//   unused entries hold INT32_MAX.
+//   wave_ev[8*w + 0 .. 3]   (pos << 4) | region for each region, sorted by pos:
+//                    the first step that reads it ("need")
+//   wave_ev[8*w + 4 .. 7]   the same for the last step that reads it ("release")
+//   (a region it never reads: both at the first step that reads a later
+//   region, or the last step); unused entries hold INT32_MAX.
 //
 // The per-row summation order is ascending input channel (the CSR order), with
 // padding zeros after the last stored block; it does not depend on the bundle

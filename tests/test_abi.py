@@ -260,6 +260,41 @@ def test_headline_plan_interleaves_two_bundles_over_strip_parts(cin, parts):
     assert (info["group_lanes"], info["waves"], info["pipe_sets"], info["regions"]) == (4, 16, 2, parts)
 
 
+def _only_channels(layer, keep):
+    """The layer with only the stored weights that keep(row, channel) allows."""
+    rp, ci, va = [0], [], []
+    for r in range(layer.cout):
+        for t in range(layer.row_ptr[r], layer.row_ptr[r + 1]):
+            if keep(r, layer.col_idx[t]):
+                ci.append(layer.col_idx[t])
+                va.append(layer.values[t])
+        rp.append(len(ci))
+    layer.row_ptr, layer.col_idx = np.array(rp, np.int32), np.array(ci, np.int32)
+    layer.values = np.array(va, np.float32)
+    return layer
+
+
+@pytest.mark.parametrize("cin,cout,regions,keep", [
+    (120, 96, 0, lambda r, c: r >= 16),                   # wavefronts whose rows are all empty
+    (512, 256, 3, lambda r, c: r % 2 or c < 170),
+    (512, 64, 4, lambda r, c: c // 128 == r // 16),       # each wavefront reads one part
+    (512, 64, 4, lambda r, c: c // 128 == 3 - r // 16),
+    (512, 512, 0, lambda r, c: c >= 400),                 # nobody reads the first parts
+    (512, 512, 0, lambda r, c: False),
+])
+def test_wavefronts_wait_for_the_strip_parts_that_they_release(cin, cout, regions, keep):
+    """The counts of parts done are summed over the wavefronts, so each may
+    count only parts that it waited for, those that it never reads included
+    (checked by the unpacking, which walks the streams as the kernel does)."""
+    layer = _only_channels(make_layer(cin, cout, 1, 1, 1, 0.9, seed=3, with_x=False), keep)
+    h = _create(layer, options=_host_opts(kernel=1, regions=regions))
+    try:
+        rp, ci, va = sp.spconv_plan_unpack_interleaved(h)
+    finally:
+        sp.spconv_destroy(h)
+    assert np.array_equal(rp, layer.row_ptr) and np.array_equal(ci, layer.col_idx) and np.array_equal(va, layer.values)
+
+
 def test_two_sets_refused_when_accumulators_do_not_fit():
     # 1x4 blocks take 8 lanes per block row: 4 x 8 accumulators per set
     layer = make_layer(256, 512, 1, 1, 1, 0.9, block_rows=4, seed=1, with_x=False)

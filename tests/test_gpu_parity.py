@@ -349,3 +349,20 @@ def test_dense_weight_with_2x2_blocks_plans_like_the_blocked_arrays():
     finally:
         p1.close()
         p2.close()
+
+
+@pytest.mark.parametrize("cin,cout,s,n,keep", [
+    (120, 96, 0.95, 384, lambda r, c: r >= 16),         # wavefronts without a stored weight
+    (512, 256, 0.95, 256, lambda r, c: c // 171 == r % 3),
+    (512, 256, 0.95, 256, lambda r, c: r % 4 > 0 and c >= 300),
+])
+def test_strip_rounds_with_wavefronts_that_skip_strip_parts(cin, cout, s, n, keep):
+    """Several rounds of tiles through the pipelined kernel, where some
+    wavefronts read no channel of some strip parts (or of none): every wait
+    ends and no part is refilled while another wavefront reads it."""
+    from test_abi import _only_channels
+    layer = _only_channels(make_layer(cin, cout, 14, 14, n, s, act="relu", seed=n + cout), keep)
+    note("strip skipped parts %d -> %d" % (cin, cout))
+    y = gpu_run(layer, kernel=1)  # checks the plan's error word
+    assert_parity(layer, y, what="%d -> %d" % (cin, cout))
+    assert np.array_equal(y.view(np.uint32), gpu_run(layer, kernel=2).view(np.uint32))
