@@ -87,6 +87,7 @@ struct DevicePlan {
     int32_t groups = 0;          // of the streams (0: the plan has none)
     int32_t max_row = 0;         // stored weights of the longest output channel
     int32_t nnz = 0;             // and of all
+    int64_t max_wave_cost = 0;   // LDS-strip kernel: the longest wavefront's slots and epilogues a tile
     // a pass over one channel range of a wider input (spconv_api.cpp): X's
     // channels per image (0: cin), and whether the pass adds to the partial
     // sums already in Y (every pass but the first)
@@ -139,9 +140,10 @@ hipError_t launch_half(const DevicePlan &p, const void *x, void *y, int32_t m, i
 
 // Whether a run of `images` planes of hw columns is faster on the row kernel
 // for few columns, and on the LDS row kernel (image_bytes: the larger of one
-// image of x and of y), than on the plan's other kernels.
+// image of x and of y), than on the plan's other kernels (`other`: the one it
+// takes of them, numbered as spconv_run_kernel).
 bool rows_pay(const DevicePlan &p, int64_t images, int64_t hw);
-bool strip_rows_pay(const DevicePlan &p, int64_t images, int64_t hw, int64_t image_bytes);
+bool strip_rows_pay(const DevicePlan &p, int64_t images, int64_t hw, int64_t image_bytes, int32_t other);
 // One launch of the row kernel for few columns over all m = N * hw columns
 // (fp32 x and y of any alignment; hw >= 4).
 hipError_t launch_rows(const DevicePlan &p, const float *x, float *y, int32_t m, int32_t hw, hipStream_t stream);

@@ -328,6 +328,7 @@ void fill_device_geometry(spconv_plan_s *pl) {
     d.hkb = h.hkb;
     d.rows = h.storage == 0 && !h.trow_ptr.empty();
     d.groups = h.glist.empty() ? 0 : h.glist.back();
+    d.max_wave_cost = h.max_wave_cost;
     d.max_row = 0;
     for (size_t r = 0; r + 1 < h.trow_ptr.size(); ++r)
         d.max_row = std::max(d.max_row, (h.trow_ptr[r + 1] & ~spconv::kRowSplit) - (h.trow_ptr[r] & ~spconv::kRowSplit));
@@ -347,13 +348,12 @@ spconv_run_kernel choose_kernel(const spconv_plan_s *pl, const spconv::DevicePla
         return SPCONV_RUN_PASSES;
     if (spconv::half_runs(d, images, hw, image_bytes))
         return SPCONV_RUN_HALF;
-    if (spconv::strip_rows_pay(d, images, hw, image_bytes))
-        return SPCONV_RUN_LDS_ROWS;
-    if (d.use_outer || (d.outer_min_cols > 0 && m >= d.outer_min_cols))
-        return SPCONV_RUN_OUTER;
-    if (d.use_indexed || (d.indexed_min_cols > 0 && m >= d.indexed_min_cols))
-        return SPCONV_RUN_INDEXED;
-    return d.kernel == spconv::KERNEL_DIRECT ? SPCONV_RUN_DIRECT : SPCONV_RUN_STRIP;
+    const spconv_run_kernel other =
+        d.use_outer || (d.outer_min_cols > 0 && m >= d.outer_min_cols)         ? SPCONV_RUN_OUTER
+        : d.use_indexed || (d.indexed_min_cols > 0 && m >= d.indexed_min_cols) ? SPCONV_RUN_INDEXED
+        : d.kernel == spconv::KERNEL_DIRECT                                    ? SPCONV_RUN_DIRECT
+                                                                               : SPCONV_RUN_STRIP;
+    return spconv::strip_rows_pay(d, images, hw, image_bytes, other) ? SPCONV_RUN_LDS_ROWS : other;
 }
 
 bool ranges_overlap(const void *a, size_t abytes, const void *b, size_t bbytes) {

@@ -22,7 +22,7 @@
 // are not more.  So 16 wavefronts a compute unit, groups of 4 weights with 8
 // scalar instructions to 20 vector ones, one wait a group.  Against the kernels
 // it replaces (us): 24 -> 144 @ 56 x 56 batch 128 63 -> 55, 144 -> 24 77 -> 67, 96 ->
-// 576 @ 14 x 14 35 -> 29, 160 -> 960 @ 7 x 7 34 -> 24, 128 -> 256 @ 28 x 28 batch 64
+// 576 @ 14 x 14 29 -> 26, 160 -> 960 @ 7 x 7 34 -> 24, 128 -> 256 @ 28 x 28 batch 64
 // 35 -> 28, 128 -> 128 @ 56 x 56 batch 64 64.4 -> 61.7 (70% sparse 130 -> 92, 1 x 4
 // 92 -> 65), 32 -> 64 @ 112 x 112 68.6 -> 66.9, 144 -> 24 @ 56 x 56 1 x 4 130 -> 39.
 //
@@ -181,7 +181,6 @@ struct SArgs {
     float lo, hi;            // the activation as a clamp
 };
 
-constexpr int64_t kRoundUnits = 64 * 256;  // units of one round of the largest tiles over 256 compute units
 constexpr int kStage = kRowMaxCin / 16;  // 16-byte vectors of the next tile a thread holds
 
 typedef uint32_t u4v __attribute__((ext_vector_type(4), aligned(4)));
@@ -372,38 +371,122 @@ bool rows_pay(const DevicePlan &p, int64_t images, int64_t hw) {
     return here < there;
 }
 
-// From a sweep of 20 layers at 2 to 3 batches (microseconds, the other kernels
-// against this one).  It needs tiles for the whole card: about 8192 units (96 ->
-// 96 @ 20 x 20: 3200 units 6.2 against 6.9, 12800 units 20.7 against 13.8; 144 ->
-// 24 @ 56 x 56: 6272 units 8.5 against 9.1, 12544 units 16.0 against 11.1), fewer
-// where many rows share a tile (48 -> 512 @ 7 x 7, batch 256: 27.6 against 11.9;
-// 24 -> 144 @ 56 x 56, batch 8: 12.6 against 8.5).  Planes that are not a multiple
-// of 4 cost the others element accesses and this one nothing (100 -> 1000 @ 13 x
-// 13, batch 8: 14.9 against 11.2; 158 -> 120 @ 33 x 33, batch 10: 16.7 against
-// 10.2).  The widest inputs (2 columns a lane) win by less: 160 -> 32 @ 28 x 28,
-// batch 128: 23.8 against 25.2, 160 -> 960 @ 7 x 7, batch 128: 33.8 against 24.4.
-// 57 .. 64 sparse rows are 15 or 16 blocks of 4, one for each wavefront of the
-// strip kernel, which then wins on more than one round of tiles (128 -> 64 @ 56
-// x 56, batch 64: 45.4 against 48.3, 144 -> 64 45.9 against 51.8; but 128 -> 64
-// @ 28 x 28 16.8 against 14.3, and with 12 blocks, 128 -> 48, 50.3 against 41.2,
-// or 80% sparse 97.8 against 56.0).
-bool strip_rows_pay(const DevicePlan &p, int64_t images, int64_t hw, int64_t image_bytes) {
+namespace {
+
+// How a run is cut into tiles (SArgs), on one of two forms: 64 units, 4 columns
+// a lane, by two workgroups of 8 wavefronts a compute unit while two tiles fit
+// in its LDS; past that 32 units, 2 columns a lane, by two of 8, or (wide) 64
+// units, 4 columns a lane, by one of 16.
+struct StripRows {
+    int v;
+    int32_t waves, tunits, slots, rounds, rest, parts;
+    double us;  // estimated time
+};
+
+// The estimate: a wavefront's groups of 4 weights (at least the longest row's) at
+// 0.148 us (0.211 by 16 wavefronts) per 100, times its tiles, plus staging and
+// traffic.  Against 5000 random layers of 8 .. 160 channels, 8 .. 1280 outputs,
+// 50 .. 98% sparse, on 256 .. 100000 units: within 10% (one sigma).
+StripRows strip_rows_form(const DevicePlan &p, int64_t all, bool wide) {
+    const int32_t cus = std::max(p.num_cus, 8);
+    const int32_t half = static_cast<int32_t>(kMaxLdsBytes / 2 / (16 * (p.cin + 1)));
+    StripRows s;
+    s.v = half >= 64 || wide ? 4 : 2;
+    s.waves = wide ? 16 : 8;
+    s.tunits = wide ? 64 : std::min(16 * s.v, half);
+    const int64_t round = 64 * static_cast<int64_t>(cus);  // units of one round of the largest tiles
+    if (wide && all > 3 * round) {
+        // few whole rounds: the same number of units to every workgroup (128 ->
+        // 128 @ 56 x 56, batch 64: 64.2 us against 65.6 with a remainder)
+        const int64_t n = (all + round - 1) / round * (cus / 8 * 8);
+        s.tunits = static_cast<int32_t>(std::min<int64_t>(64, (all + n - 1) / n));
+    }
+    s.slots = (s.waves == 8 ? 2 : 1) * cus / 8 * 8;
+    const int64_t tiles = (all + s.tunits - 1) / s.tunits;
+    s.rounds = static_cast<int32_t>(tiles / s.slots);
+    s.rest = static_cast<int32_t>(tiles - static_cast<int64_t>(s.rounds) * s.slots);
+    s.parts = 1;
+    while (2 * s.parts <= kRowLists / s.waves && static_cast<int64_t>(s.rest) * 2 * s.parts <= s.slots)
+        s.parts *= 2;
+    const double turns = s.rounds + (s.rest ? 1.0 / s.parts : 0.0);
+    const double groups = std::max<double>(static_cast<double>(p.groups) / s.waves, p.max_row / 4.0);
+    const double mb = 16e-6 * static_cast<double>(all) * (p.cin + p.cout);
+    s.us = wide ? 4.8 + 0.211 * turns * groups + 0.02 * turns * p.cin + 0.08 * mb
+                : 4.5 + 0.148 * turns * groups + (s.rounds ? 0.01 * turns * p.cin : 0.0) + 0.11 * mb;
+    return s;
+}
+
+// The faster form.  Over 80 .. 159 channels the wide one wins with the tiles and
+// the weights to spread over it (128 -> 256 @ 28 x 28, batch 64: 28 us against 33;
+// 96 -> 576 @ 14 x 14, batch 128: 26 against 35; 144 -> 24 @ 56 x 56, batch 128: 80
+// against 67, whose wavefronts wait for the longest row); the estimates pick the
+// slower one by more than 5% on 5% of the layers above.
+StripRows strip_rows_shape(const DevicePlan &p, int64_t all) {
+    const StripRows a = strip_rows_form(p, all, false);
+    if (a.v == 4 || p.cin >= 160)  // (the wide form's tile and its row of zeros fill the LDS up to 159 channels)
+        return a;
+    const StripRows b = strip_rows_form(p, all, true);
+    return b.us < a.us ? b : a;
+}
+
+// The estimated time of the run on `other`, the kernel it takes otherwise, over
+// the same layers: within 14 to 18% (one sigma), 24% on the element paths (hw not a
+// multiple of 4) of blocked weights.
+double other_us(const DevicePlan &p, int64_t images, int64_t hw, int32_t other) {
+    const double units = static_cast<double>(images) * ((hw + 3) / 4);
+    const double x = 4e-6 * images * hw * p.cin, y = 4e-6 * images * hw * p.cout;  // MB
+    const bool vec = hw % 4 == 0;
+    if (other == 3)  // register-indexed
+        return 1.9 + 0.157e-6 * units * p.nnz + 0.339 * x + 0.155 * y + 0.28 * p.max_row;
+    if (other == 4)  // lockstep, 1 x 4 blocks
+        return vec ? 4.0 + 0.076e-6 * units * p.nnz + 0.594 * x + 0.128 * y + 0.0285 * p.max_row
+                   : 7.2 + 0.0215e-6 * units * p.nnz + 1.69 * x + 0.258 * y + 0.0412 * p.max_row;
+    // LDS strip: the longest wavefront's slots times the vectors of a lane, per
+    // tile; tiles left after whole rounds are shared as its launch shares them
+    const int64_t cus = std::max(p.num_cus, 8);
+    const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(kMaxLdsBytes / std::max(p.lds_bytes, 1), 32 / p.waves));
+    const int64_t tiles = (images * hw + p.tile_cols - 1) / p.tile_cols, slots = cus * per_cu;
+    const int64_t rest = tiles % slots;
+    int64_t parts = 1;
+    while (rest && 2 * parts <= p.max_parts && 2 * parts <= slots / 8 / ((rest + 7) / 8))
+        parts *= 2;
+    const double turns = static_cast<double>(tiles / slots) + (rest ? 1.0 / parts : 0.0);
+    const double work = turns * static_cast<double>(p.max_wave_cost) * 16 / p.group_lanes;
+    if (p.k == 1)
+        return vec ? 4.5 + 0.0593 * work + 0.161 * (x + y) + 0.0009 * p.cin
+                   : 5.7 + 0.040 * work + 0.109 * x + 0.635 * y + 0.0116 * p.cin;
+    return vec ? 4.6 + 0.0526 * work + 0.085 * x + 0.214 * y + 0.0059 * p.cin
+               : 4.85 + 0.100 * work + 0.767 * y + 0.0212 * p.cin;
+}
+
+}  // namespace
+
+// Taken where its estimate is below the other kernel's, by up to a fifth above on
+// planes that are not a multiple of 4, which cost the others element accesses
+// and this one nothing (100 -> 1000 @ 13 x 13, batch 8: 14.9 against 11.2; their
+// estimate is the rougher one).  It needs tiles for the card: about 8192 units
+// (96 -> 96 @ 20 x 20: 3200 units 6.2 against 6.9, 12800 units 20.7 against 13.8),
+// fewer where many rows share a tile (48 -> 512 @ 7 x 7, batch 256: 27.6 against
+// 11.9; 24 -> 144 @ 56 x 56, batch 8: 12.6 against 8.5).  Where the estimates turn it
+// down: long rows, whose weights cost this kernel as much LDS bandwidth and more
+// issue (144 -> 1024 @ 28 x 28, batch 24, 80% sparse: 40 against 62; 160 -> 768,
+// 1 x 4, half dense, batch 12: 25 against 77).  Of 3500 random runs 2% are slower
+// than on the other kernel by more than 5% (the worst 1.5 times); by a rule on
+// sizes alone it was 7% (2.8 times), and half of those with 80 .. 160 channels,
+// 256 or more outputs and 1024 .. 8192 units.
+bool strip_rows_pay(const DevicePlan &p, int64_t images, int64_t hw, int64_t image_bytes, int32_t other) {
     if (p.groups == 0 || hw < 4)
         return false;
     const int64_t units = (hw + 3) / 4, all = images * units;
     // the images of a tile must span less than 2^31 bytes
     if ((63 / units + 2) * image_bytes >= (int64_t(1) << 31) - 16 || all > (int64_t(1) << 29))
         return false;
-    if (hw % 4 != 0)
-        return all >= 256;
-    if (p.cout >= 256 && all >= 1024)
-        return true;
-    if (p.cin <= 64 && p.cout >= 128 && all >= 4096)
-        return true;
-    if (p.k == 1 && p.cin > 80 && p.cout > 56 && p.cout <= 64 && all > kRoundUnits &&
-        p.nnz <= 0.16 * p.cin * p.cout)
-        return false;
-    return all >= 8192 && p.cin < 156;
+    const int64_t least = hw % 4 != 0                       ? 256
+                          : p.cout >= 256                   ? 1024
+                          : p.cin <= 64 && p.cout >= 128 ? 4096
+                                                            : 8192;
+    return all >= least &&
+           strip_rows_shape(p, all).us < (hw % 4 != 0 ? 1.2 : 1.0) * other_us(p, images, hw, other);
 }
 
 hipError_t launch_rows(const DevicePlan &p, const float *x, float *y, int32_t m, int32_t hw, hipStream_t stream) {
@@ -464,43 +547,20 @@ hipError_t launch_strip_rows(const DevicePlan &p, const float *x, float *y, int3
     a.y_bytes = y_bytes;
     a.lo = p.act == 0 ? -__builtin_huge_valf() : 0.0f;
     a.hi = p.act == 2 ? 6.0f : __builtin_huge_valf();
-    const int32_t cus = std::max(p.num_cus, 1);
-    const int64_t all = static_cast<int64_t>(a.images) * a.units;
-    // Tiles of 64 units, 4 columns a lane, by two workgroups of 8 wavefronts a
-    // compute unit while two tiles fit in its LDS; past that by one of 16, given
-    // the tiles and enough weights to spread over it (128 -> 256 @ 28 x 28, batch
-    // 64: 28 us against 33; 96 -> 576 @ 14 x 14, batch 128: 29 against 37), else 32
-    // units, 2 columns a lane, by two of 8 (144 -> 24 @ 56 x 56, batch 128: 67
-    // against 80, whose wavefronts wait for the longest row; 160 -> 960 @ 7 x 7,
-    // batch 128: 24 against 33).
-    const int32_t half = static_cast<int32_t>(kMaxLdsBytes / 2 / (16 * (p.cin + 1)));
-    const bool big = half < 64 && p.cin < 160 && p.groups >= 256 && all >= 32 * static_cast<int64_t>(cus);
-    const int v = half >= 64 || big ? 4 : 2;
-    const int32_t waves = big ? 16 : 8;
-    a.tunits = big ? 64 : std::min(16 * v, half);
-    if (big && all > 3 * kRoundUnits) {
-        // few whole rounds: the same number of units to every workgroup (128 ->
-        // 128 @ 56 x 56, batch 64: 64.2 us against 65.6 with a remainder)
-        const int64_t rounds = (all + kRoundUnits - 1) / kRoundUnits, n = rounds * (cus / 8 * 8);
-        if (n > 0)
-            a.tunits = static_cast<int32_t>(std::min<int64_t>(64, (all + n - 1) / n));
-    }
+    const StripRows s = strip_rows_shape(p, static_cast<int64_t>(a.images) * a.units);
+    a.tunits = s.tunits;
+    a.row_bytes = 16 * a.tunits;
+    a.rounds = s.rounds;
+    a.rest = s.rest;
+    a.parts = s.parts;
     // (a pass of the workgroup stages 4 / v * waves channels)
     static_assert(kRowMaxCin <= 16 * kStage && kMaxLdsBytes / 2 / (16 * 64) - 1 <= 8 * kStage, "staged in kStage passes");
-    a.row_bytes = 16 * a.tunits;
-    const int32_t slots = (waves == 8 ? 2 : 1) * cus / 8 * 8;
-    const int64_t tiles = (all + a.tunits - 1) / a.tunits;
-    a.rounds = static_cast<int32_t>(tiles / slots);
-    a.rest = static_cast<int32_t>(tiles - static_cast<int64_t>(a.rounds) * slots);
-    a.parts = 1;
-    while (2 * a.parts <= kRowLists / waves && static_cast<int64_t>(a.rest) * 2 * a.parts <= slots)
-        a.parts *= 2;
     a.nxcd = 8;
-    const int64_t grid = a.rounds > 0 ? slots : (static_cast<int64_t>(a.rest) * a.parts + 7) / 8 * 8;
-    const auto kernel = p.splits ? (v == 4 ? strip_rows_kernel<4, true> : strip_rows_kernel<2, true>)
-                                 : (v == 4 ? strip_rows_kernel<4, false> : strip_rows_kernel<2, false>);
+    const int64_t grid = a.rounds > 0 ? s.slots : (static_cast<int64_t>(a.rest) * a.parts + 7) / 8 * 8;
+    const auto kernel = p.splits ? (s.v == 4 ? strip_rows_kernel<4, true> : strip_rows_kernel<2, true>)
+                                 : (s.v == 4 ? strip_rows_kernel<4, false> : strip_rows_kernel<2, false>);
     hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(grid)),
-                       dim3(64 * waves), (p.cin + 1) * a.row_bytes, stream, a);
+                       dim3(64 * s.waves), (p.cin + 1) * a.row_bytes, stream, a);
     return hipGetLastError();
 }
 

@@ -44,13 +44,19 @@ STRIP = [
     (160, 260, 7, 7, 90, 0.85, 1, "relu"),     # the widest input, 31-unit tiles
     (161, 260, 7, 7, 90, 0.85, 1, "relu"),     # past it
     (24, 144, 2, 2, 4200, 0.85, 1, "none"),    # planes of one unit
+    (159, 300, 21, 21, 42, 0.9, 1, "relu6"),   # the widest input of the 16 wavefronts, odd planes
+    (96, 576, 14, 14, 128, 0.85, 1, "relu6"),  # 98 tiles of 16 wavefronts, shared by 2 parts
+    (112, 400, 9, 9, 200, 0.9, 1, "none"),     # 66 of them by 2, odd planes
+    (80, 256, 14, 14, 30, 0.95, 1, "relu"),    # 23 tiles by 4 parts
 ]
+OTHER = [(159, 300, 28, 28, 42, 0.9, 2, "relu6"), (161, 260, 7, 7, 90, 0.85, 1, "relu")]  # of these, not by the LDS kernel
 
 
 def _check(spec, what):
     cin, cout, h, w, n, s, k, act = spec
     layer = make_layer(cin, cout, h, w, n, s, block_rows=k, act=act, seed=zlib.crc32(repr(spec).encode()) % 1000)
     note("%s %s" % (what, spec))
+    assert_runs(layer, "strip" if h * w < 4 or spec in OTHER else what)
     y = gpu_run(layer)
     assert_parity(layer, y, what=str(spec))
     assert np.array_equal(y.view(np.uint32), gpu_run(layer, kernel=2).view(np.uint32))
@@ -58,12 +64,12 @@ def _check(spec, what):
 
 @pytest.mark.parametrize("spec", FEW, ids=lambda s: "%d-%d-%dx%d-n%d-s%g-k%d-%s" % s)
 def test_few_columns_match_oracle_and_direct_kernel(spec):
-    _check(spec, "rows few")
+    _check(spec, "rows")
 
 
 @pytest.mark.parametrize("spec", STRIP, ids=lambda s: "%d-%d-%dx%d-n%d-s%g-k%d-%s" % s)
 def test_lds_rows_match_oracle_and_direct_kernel(spec):
-    _check(spec, "rows lds")
+    _check(spec, "lds rows")
 
 
 @pytest.mark.parametrize("n", [3, 260])
@@ -81,6 +87,7 @@ def test_rows_without_weights_and_a_long_row(n):
     layer.row_ptr, layer.col_idx = np.array(rp, np.int32), np.array(ci, np.int32)
     layer.values = rng.standard_normal(len(ci)).astype(np.float32)
     note("rows empty n=%d" % n)
+    assert_runs(layer, "rows" if n == 3 else "lds rows")
     y = gpu_run(layer)
     assert_parity(layer, y, what="empty rows")
     assert np.array_equal(y.view(np.uint32), gpu_run(layer, kernel=2).view(np.uint32))
@@ -94,6 +101,7 @@ def test_rows_unaligned_pointers(hw, n):
     from paper_1911_09723_amd import Plan
     layer = make_layer(40, 50, hw[0], hw[1], n, 0.8, act="relu", seed=5)
     note("rows unaligned %s n=%d" % (hw, n))
+    assert_runs(layer, "strip" if hw == (1, 2) else "rows" if n == 5 else "lds rows")
     ref = gpu_run(layer)
     plan = Plan.from_layer(layer)
     try:
@@ -120,6 +128,7 @@ def test_rows_infinities_and_nans_stay_on_their_rows(hw, n, act):
     x[n - 1, 69, -1, -1] = np.nan
     x[n - 1, 12, 0, 0] = np.inf
     note("rows non-finite %s n=%d %s" % (hw, n, act))
+    assert_runs(layer, "strip" if hw == (1, 1) else "rows" if n == 4 else "lds rows")
     y = gpu_run(layer, x=x).astype(np.float64)
     wd = densify(45, 70, 1, layer.row_ptr, layer.col_idx, layer.values)
     stored = densify(45, 70, 1, layer.row_ptr, layer.col_idx, np.ones_like(layer.values)) > 0
@@ -164,6 +173,7 @@ def test_split_rows_keep_the_strip_kernels_sums(spec):
     finally:
         plan.close()
     note("rows split %s" % (spec,))
+    assert_runs(layer, "rows" if n == 1 else "lds rows")
     y = gpu_run(layer)
     assert_parity(layer, y, what=str(spec))
     assert np.array_equal(y.view(np.uint32), gpu_run(layer, kernel=1).view(np.uint32))

@@ -56,6 +56,24 @@ AUTO = [
 ]
 
 
+# Runs where the other kernel is the faster one by half to three times (us on the LDS rows and on it)
+LONG_ROWS = [
+    (144, 1024, 0.8, {}, 24, 28, 28, "strip"),                   # 62, 40
+    (136, 768, 0.5, {}, 189, 10, 10, "strip"),                   # 93, 58
+    (80, 818, 0.7, {}, 44, 20, 20, "strip"),                     # 45, 33
+    (96, 576, 0.5, {}, 6, 56, 56, "strip"),                      # 59, 41
+    (152, 512, 0.5, {"block_rows": 2}, 87, 14, 14, "strip"),     # 77, 44
+    (120, 576, 0.5, {"block_rows": 4}, 70, 20, 20, "outer"),     # 68, 40
+    (160, 768, 0.5, {"block_rows": 4}, 12, 28, 28, "outer"),     # 77, 25
+    (144, 960, 0.8, {"block_rows": 4}, 180, 12, 12, "outer"),    # 58, 34
+]
+
+
+@pytest.mark.parametrize("cin,cout,s,kw,n,h,w,name", LONG_ROWS)
+def test_long_rows_stay_off_the_lds_row_kernel(cin, cout, s, kw, n, h, w, name):
+    assert run_kernel(layer_of(cin, cout, s, **kw), n, h, w) == name
+
+
 @pytest.mark.parametrize("cin,cout,kw,n,h,w,name", AUTO)
 def test_automatic_choice(cin, cout, kw, n, h, w, name):
     assert run_kernel(layer_of(cin, cout, **kw), n, h, w) == name
