@@ -355,6 +355,10 @@ __global__ void __launch_bounds__(1024) strip_rows_kernel(SArgs a) {
 // with few rows), those for wide inputs 13.  512 -> 512 @ 14 x 14: one image 6.7
 // against 13.7, four 8.5 against 14.4, eight 13.4 against 14.9; 32 -> 64 @ 56 x
 // 56: one image 3.3 against 5.1, four 4.5 against 5.8, eight 6.2 against 6.2.
+// Every output channel reads X again, from L2 while it fits there: past 6 MB of X
+// a wavefront's reads take longer, up to 2.3 times from 14 MB (512 -> 64 @ 28 x
+// 28, 11 images: 16.7 against 9.0; of 2500 random runs taken here, 35 were slower
+// than on the other kernel without this term, up to 1.95 times, 18 with it).
 bool rows_pay(const DevicePlan &p, int64_t images, int64_t hw) {
     if (!p.rows || hw < 4)
         return false;
@@ -363,7 +367,9 @@ bool rows_pay(const DevicePlan &p, int64_t images, int64_t hw) {
         return false;
     const double mean = static_cast<double>(p.nnz) / p.cout;
     const double waves = static_cast<double>((units + 63) / 64) * p.cout;
-    const double here = 2.3 + std::max(0.062 * p.max_row, waves * (0.5 + 0.053 * mean) * 1e-3);
+    const double x_mb = 16e-6 * static_cast<double>(units) * p.cin;
+    const double read = 0.053 * std::min(2.3, std::max(1.0, x_mb / 6.0));
+    const double here = 2.3 + std::max(0.062 * p.max_row, waves * (0.5 + read * mean) * 1e-3);
     double there = p.k == 4 ? 4.0 + 0.008 * p.cin
                             : 4.0 + 0.009 * p.cin + 0.1 * mean * std::min(1.0, p.cout / 128.0);
     if (p.kernel == KERNEL_DIRECT)

@@ -69,8 +69,17 @@ LONG_ROWS = [
 ]
 
 
-@pytest.mark.parametrize("cin,cout,s,kw,n,h,w,name", LONG_ROWS)
-def test_long_rows_stay_off_the_lds_row_kernel(cin, cout, s, kw, n, h, w, name):
+# Runs whose X is past the L2, which the row kernel reads again for every output channel
+WIDE_X = [
+    (512, 64, 0.9, {}, 11, 28, 28, "strip"),                     # 17 us on the row kernel, 9 on this one
+    (1024, 91, 0.9, {}, 8, 20, 20, "outer"),                     # 18, 9
+    (512, 45, 0.9, {}, 3, 56, 56, "strip"),                      # 14, 8
+    (1160, 128, 0.95, {}, 22, 14, 14, "outer"),                  # 20, 13
+]
+
+
+@pytest.mark.parametrize("cin,cout,s,kw,n,h,w,name", LONG_ROWS + WIDE_X)
+def test_row_kernels_only_where_they_are_the_faster_ones(cin, cout, s, kw, n, h, w, name):
     assert run_kernel(layer_of(cin, cout, s, **kw), n, h, w) == name
 
 
