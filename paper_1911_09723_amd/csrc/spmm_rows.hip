@@ -357,8 +357,10 @@ __global__ void __launch_bounds__(1024) strip_rows_kernel(SArgs a) {
 // 56: one image 3.3 against 5.1, four 4.5 against 5.8, eight 6.2 against 6.2.
 // Every output channel reads X again, from L2 while it fits there: past 6 MB of X
 // a wavefront's reads take longer, up to 2.3 times from 14 MB (512 -> 64 @ 28 x
-// 28, 11 images: 16.7 against 9.0; of 2500 random runs taken here, 35 were slower
-// than on the other kernel without this term, up to 1.95 times, 18 with it).
+// 28, 11 images: 16.7 against 9.0), and past 4 MB the chain of the longest row up
+// to 1.5 times (940 -> 128 @ 10 x 10, 16 images: 14.4 against 8.8).  Of 2500 random
+// runs taken here 16 are slower than on the other kernel by more than 5%, up to 1.6
+// times; without the two factors 35, up to 1.95.
 bool rows_pay(const DevicePlan &p, int64_t images, int64_t hw) {
     if (!p.rows || hw < 4)
         return false;
@@ -369,7 +371,8 @@ bool rows_pay(const DevicePlan &p, int64_t images, int64_t hw) {
     const double waves = static_cast<double>((units + 63) / 64) * p.cout;
     const double x_mb = 16e-6 * static_cast<double>(units) * p.cin;
     const double read = 0.053 * std::min(2.3, std::max(1.0, x_mb / 6.0));
-    const double here = 2.3 + std::max(0.062 * p.max_row, waves * (0.5 + read * mean) * 1e-3);
+    const double chain = 0.062 * std::min(1.5, std::max(1.0, x_mb / 4.0));
+    const double here = 2.3 + std::max(chain * p.max_row, waves * (0.5 + read * mean) * 1e-3);
     double there = p.k == 4 ? 4.0 + 0.008 * p.cin
                             : 4.0 + 0.009 * p.cin + 0.1 * mean * std::min(1.0, p.cout / 128.0);
     if (p.kernel == KERNEL_DIRECT)

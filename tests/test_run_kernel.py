@@ -75,6 +75,8 @@ WIDE_X = [
     (1024, 91, 0.9, {}, 8, 20, 20, "outer"),                     # 18, 9
     (512, 45, 0.9, {}, 3, 56, 56, "strip"),                      # 14, 8
     (1160, 128, 0.95, {}, 22, 14, 14, "outer"),                  # 20, 13
+    (940, 128, 0.9, {}, 16, 10, 10, "outer"),                    # 14, 9 (a long chain of such reads)
+    (1118, 184, 0.9, {}, 2, 28, 28, "outer"),                    # 16, 10
 ]
 
 
