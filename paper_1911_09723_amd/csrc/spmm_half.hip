@@ -490,9 +490,13 @@ HalfShape half_shape(const DevicePlan &p, int64_t images, int64_t hw, int64_t im
     s.lds = half_lds_bytes(kb, s.parts);
     // wavefronts: 16 a compute unit, in one workgroup where LDS or the number
     // of tiles leaves no second one (192 -> 1152 @ 7 x 7, batch 512, 256
-    // tiles: 34 us against 44 with 8); fewer in short runs, whose tiles are
-    // shared by row groups, and for few rows
-    s.waves = 2 * s.tiles < cus                                         ? (s.lds > kMaxLdsBytes / 2 ? 8 : 2)
+    // tiles: 34 us against 44 with 8).  Short runs share each tile among
+    // workgroups by row groups: of 8 wavefronts where a compute unit has at least
+    // 4 row groups, else of 4 (with 2, the card is short of wavefronts: 155 ->
+    // 1540 @ 1 x 1, 1931 images, 44 us against 24 with 8; over 2000 random runs of
+    // fewer than 128 tiles 8% behind 4 and, by row groups, 4 to 85% behind 8; 16
+    // are slower).  Fewer for few rows.
+    s.waves = 2 * s.tiles < cus ? (s.lds > kMaxLdsBytes / 2 || s.tiles * s.rgroups >= 4 * cus ? 8 : 4)
               : s.lds > kMaxLdsBytes / 2 || s.tiles <= 3 * cus / 2 ? 16
                                                                    : 8;
     if (row_tiles16 <= 4 && kb > 1)
