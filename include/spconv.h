@@ -280,7 +280,7 @@ typedef struct {
     int32_t host_only;   /* 1: plan on the host only, no device memory; spconv_run refuses it */
     int32_t kernel;      /* 0 = choose automatically at each run (spconv_plan_run_kernel says
                             which): fp16, the half kernel up to 1216 input channels and 16 MiB
-                            of dense weights; fp32, a row kernel for runs of few columns, or of
+                            of dense weights, unless few weights are stored; fp32, a row kernel for runs of few columns, or of
                             up to 160 input channels over LDS tiles, where it measured faster;
                             else the LDS-strip or direct-load kernel, or, for
                             runs with enough columns on layers where it measured faster, the

@@ -129,10 +129,13 @@ hipError_t launch_outer(const DevicePlan &p, const void *x, void *y, int32_t m, 
 
 // Once per plan: allow the half kernel its LDS.
 hipError_t prepare_half(const DevicePlan &p);
+// Whether runs on planes of hw columns are faster on the half kernel than on
+// the plan's others (`lockstep`: they would take the lockstep kernel).
+bool half_pays(const DevicePlan &p, int64_t hw, bool lockstep);
 // Whether a run fits one launch of the half kernel: a launch has fewer than
 // 2^32 threads, and its workgroups take one tile each (the other kernels loop
 // over tiles).
-bool half_runs(const DevicePlan &p, int64_t images, int64_t hw, int64_t image_bytes);
+bool half_fits(const DevicePlan &p, int64_t images, int64_t hw, int64_t image_bytes);
 // One launch of the half kernel over all m = N * hw columns (fp16 x and y).
 // `vec` != 0 promises hw a multiple of 4 and 8-byte aligned x and y.
 hipError_t launch_half(const DevicePlan &p, const void *x, void *y, int32_t m, int32_t hw, int32_t vec,

@@ -346,13 +346,13 @@ spconv_run_kernel choose_kernel(const spconv_plan_s *pl, const spconv::DevicePla
         return SPCONV_RUN_ROWS;
     if (!pl->passes.empty())
         return SPCONV_RUN_PASSES;
-    if (spconv::half_runs(d, images, hw, image_bytes))
-        return SPCONV_RUN_HALF;
     const spconv_run_kernel other =
         d.use_outer || (d.outer_min_cols > 0 && m >= d.outer_min_cols)         ? SPCONV_RUN_OUTER
         : d.use_indexed || (d.indexed_min_cols > 0 && m >= d.indexed_min_cols) ? SPCONV_RUN_INDEXED
         : d.kernel == spconv::KERNEL_DIRECT                                    ? SPCONV_RUN_DIRECT
                                                                                : SPCONV_RUN_STRIP;
+    if (spconv::half_pays(d, hw, other == SPCONV_RUN_OUTER) && spconv::half_fits(d, images, hw, image_bytes))
+        return SPCONV_RUN_HALF;
     return spconv::strip_rows_pay(d, images, hw, image_bytes, other) ? SPCONV_RUN_LDS_ROWS : other;
 }
 

@@ -511,9 +511,32 @@ HalfShape half_shape(const DevicePlan &p, int64_t images, int64_t hw, int64_t im
 
 }  // namespace
 
-bool half_runs(const DevicePlan &p, int64_t images, int64_t hw, int64_t image_bytes) {
+// Both sides from 5500 random runs (8 .. 1216 channels, 8 .. 1600 outputs, 50 .. 98%
+// sparse, 1 to 2048 images), which are 2.5 times as fast here as on the others.
+// The dense product and the staging cost the same however few weights are stored;
+// the strip and direct-load kernels pay by the weight, little where they read
+// whole 16-byte vectors (hw a multiple of 8).  There they win with fewer than 2
+// stored weights an input channel (slower here in 35% of those runs, even on
+// average), fewer than 4 past 320 channels (1077 -> 10 @ 56 x 56, 98% sparse, 26
+// images: 98 us here against 9.7; 80% slower, by 1.8 times on average); elsewhere
+// only past 640 channels with fewer than 0.7 (1002 -> 12 @ 7 x 7: 92
+// against 49).  The lockstep kernel wins on planes of up to 4 columns, which fill
+// a quarter of a unit or one operand of it, past 320 channels where the products
+// count (477 -> 628 @ 2 x 2, 617 images: 16.8 against 9.0).  Of 5500 other runs 3%
+// are slower here by more than 5%, up to 1.9 times (without this rule 5%, up to
+// 10 times).
+// The rule does not look at the number of images: the matrix instruction sums in
+// another order, and an image's bits must not depend on its batch.
+bool half_pays(const DevicePlan &p, int64_t hw, bool lockstep) {
     if (p.hkb == 0)
         return false;
+    const double uses = static_cast<double>(p.nnz) / p.cin;
+    if (lockstep)
+        return hw > 4 || p.hkb <= 10 || static_cast<double>(p.cin) * p.cout < 90.0 * (p.cin + p.cout);
+    return uses >= (hw % 8 == 0 ? (p.hkb > 10 ? 4.0 : 2.0) : p.hkb > 20 ? 0.7 : 0.0);
+}
+
+bool half_fits(const DevicePlan &p, int64_t images, int64_t hw, int64_t image_bytes) {
     const HalfShape s = half_shape(p, images, hw, image_bytes);
     return s.grid * 64 * s.waves < int64_t(1) << 32;
 }

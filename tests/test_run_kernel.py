@@ -104,6 +104,24 @@ def test_layout_options_keep_the_kernels_that_they_lay_out(option):
     assert run_kernel(f16, 64, 28, 28, **{option: value}) == "strip"
 
 
+@pytest.mark.parametrize("cin,cout,s,kw,h,w,name", [
+    (1077, 10, 0.98, {}, 56, 56, "direct"),                   # us on the half kernel and on this one: 98, 9.7
+    (890, 8, 0.95, {"block_rows": 2}, 28, 28, "direct"),      # 122, 14
+    (420, 14, 0.98, {}, 28, 28, "strip"),                     # 21, 9
+    (17, 8, 0.85, {"block_rows": 2}, 20, 20, "strip"),        # 11, 5
+    (1002, 12, 0.95, {"block_rows": 4}, 7, 7, "direct"),      # 92, 49
+    (477, 628, 0.98, {"block_rows": 4}, 2, 2, "outer"),       # 17, 9
+    (112, 672, 0.9, {"block_rows": 4}, 14, 14, "half"),
+    (1077, 64, 0.9, {}, 56, 56, "half"),
+    (320, 628, 0.98, {"block_rows": 4}, 2, 2, "half"),
+])
+def test_half_kernel_where_its_products_are_worth_it(cin, cout, s, kw, h, w, name):
+    """By the layer and the plane only: an image takes the same kernel, and
+    gives the same bits, in every batch."""
+    layer = layer_of(cin, cout, s, storage="f16", **kw)
+    assert {run_kernel(layer, n, h, w) for n in (1, 26, 617, 4096)} == {name}
+
+
 def test_half_kernel_only_where_its_workgroups_fit_one_launch():
     """A launch has fewer than 2^32 threads; the half kernel's workgroups take
     one tile each, so the longest runs take the kernel that loops over tiles."""
