@@ -1,12 +1,14 @@
 """GPU parity of the half kernel (fp16 storage, the automatic choice): dense
 fragments of W on the matrix cores.
 
-Each case is compared with the oracle to the fp16 tolerance.  The sizes sit at
-the kernel's edges: input channels around blocks of 32 and 8, output channels
-around groups of 32, 16 and 4 rows, column counts around tiles of 64 and 128
-(64-column tiles where a run has few or the input is wide), planes whose
-4-column units lie in one image, straddle two (H*W not a multiple of 4) or
-more (H*W below 4), and the widest input of its range and one past it.
+Each case is compared with the oracle to the fp16 tolerance.  A tile is whole
+image planes or an even piece of one, in parts of 16 units of 4 neighbouring
+columns of a plane.  The sizes sit at the kernel's edges: input channels around
+blocks of 32 and 8, output channels around groups of 32, 16 and 4 rows, planes
+whose last unit is short (H*W not a multiple of 4) or only (H*W below 4), one,
+two and four parts at a time, wavefronts that share a row tile (large planes of
+up to 64 channels), short runs whose tiles are shared by workgroups of 4 and 8
+wavefronts, and the widest input of its range and one past it.
 """
 
 import zlib
@@ -21,19 +23,27 @@ pytestmark = pytest.mark.gpu
 
 # (cin, cout, h, w, n, sparsity, k, act)
 SHAPES = [
-    (32, 32, 8, 8, 1, 0.5, 1, "relu"),        # one tile of 64 columns, one block, one row group
-    (33, 36, 8, 8, 1, 0.8, 4, "none"),        # a block with one channel, a group with 4 rows
-    (31, 30, 4, 15, 1, 0.8, 2, "relu6"),      # ragged block, group and tile
+    (32, 32, 8, 8, 1, 0.5, 1, "relu"),        # one part, one block, two row tiles
+    (33, 36, 8, 8, 1, 0.8, 4, "none"),        # a block with one channel, a row tile with 4 rows
+    (31, 30, 4, 15, 1, 0.8, 2, "relu6"),      # ragged block and row tile, 15 units
     (7, 4, 1, 4, 1, 0.0, 4, "none"),          # the smallest vector case
     (9, 1, 1, 1, 1, 0.0, 1, "relu"),          # one column
     (40, 65, 1, 3, 7, 0.7, 1, "relu"),        # H*W below 4: element loads and stores
     (72, 100, 1, 2, 45, 0.8, 4, "none"),
-    (24, 40, 1, 1, 130, 0.5, 1, "relu6"),     # units of 4 images
-    (48, 33, 5, 5, 6, 0.8, 1, "relu"),        # 150 columns: straddling units, a ragged last unit
-    (64, 48, 3, 3, 29, 0.8, 2, "none"),       # 261 columns, H*W = 9
-    (320, 128, 7, 7, 700, 0.9, 4, "relu6"),   # 128-column tiles, odd planes, the widest at that tile
-    (321, 128, 14, 14, 90, 0.9, 1, "relu"),   # 64-column tiles
-    (128, 672, 14, 14, 96, 0.9, 4, "relu6"),  # 128-column tiles, row groups over several workgroups
+    (24, 40, 1, 1, 130, 0.5, 1, "relu6"),     # units of one column
+    (48, 33, 5, 5, 6, 0.8, 1, "relu"),        # 7 units a plane, the last of one column
+    (64, 48, 3, 3, 29, 0.8, 2, "none"),       # 3 units a plane
+    (320, 128, 7, 7, 700, 0.9, 4, "relu6"),   # two parts of two odd planes, the most blocks held in registers
+    (321, 128, 14, 14, 90, 0.9, 1, "relu"),   # one block more: two row tiles a group
+    (128, 672, 14, 14, 96, 0.9, 4, "relu6"),  # two parts, 42 row tiles for 16 wavefronts
+    (96, 160, 13, 13, 400, 0.9, 1, "none"),   # four parts of an odd plane
+    (288, 96, 12, 12, 400, 0.9, 2, "relu"),   # four parts, 9 blocks
+    (40, 240, 18, 18, 300, 0.9, 4, "relu6"),  # two wavefronts share a row tile
+    (40, 240, 17, 17, 300, 0.9, 1, "relu"),   # the same, odd planes
+    (40, 240, 28, 28, 90, 0.9, 4, "none"),    # four wavefronts
+    (33, 100, 23, 23, 120, 0.8, 1, "none"),   # the same, odd planes
+    (64, 300, 7, 7, 6, 0.8, 1, "relu"),       # a short run: workgroups of 4 wavefronts
+    (155, 1540, 1, 1, 1931, 0.95, 4, "none"), # of 8
     (1216, 40, 7, 7, 3, 0.9, 1, "relu"),      # the widest input
     (1217, 40, 7, 7, 3, 0.9, 1, "relu"),      # past it
 ]
@@ -45,6 +55,7 @@ def test_half_matches_oracle(spec):
     layer = make_layer(cin, cout, h, w, n, s, block_rows=k, storage="f16", act=act,
                        seed=zlib.crc32(repr(spec).encode()) % 1000)
     note("half %s" % (spec,))
+    assert_runs(layer, "half" if cin <= 1216 else "direct")
     assert_parity(layer, gpu_run(layer), what=str(spec))
 
 
@@ -56,6 +67,7 @@ def test_half_alignment_and_batch_do_not_change_bits(hw):
     from paper_1911_09723_amd import Plan
     layer = make_layer(72, 100, hw[0], hw[1], 5, 0.8, storage="f16", act="none", seed=3)
     note("half unaligned %s" % (hw,))
+    assert_runs(layer, "half")
     ref = gpu_run(layer)
     parts = [gpu_run(layer, x=layer.x[i:i + 1]) for i in range(5)]
     assert np.array_equal(ref.view(np.uint16), np.concatenate(parts).view(np.uint16))
@@ -95,6 +107,25 @@ def test_half_longest_runs_take_another_kernel():
     finally:
         plan.close()
         torch.cuda.empty_cache()
+
+
+def test_half_keeps_subnormals():
+    """Subnormal fp16 values of X and of W reach the products: the result is
+    exact (one weight of 1, or of 2^-20 times powers of two, a row)."""
+    c = 96
+    rng = np.random.default_rng(6)
+    layer = make_layer(c, c, 7, 7, 3, 0.5, storage="f16", act="none", seed=6)
+    layer.row_ptr, layer.col_idx = np.arange(c + 1, dtype=np.int32), np.arange(c, dtype=np.int32)
+    layer.bias = np.zeros(c, np.float32)
+    layer.values = np.ones(c, np.float32)
+    layer.x = (rng.integers(-1023, 1024, layer.x.shape) * 2.0 ** -24).astype(np.float16)
+    note("half subnormal x")
+    assert_runs(layer, "half")
+    assert np.array_equal(gpu_run(layer), layer.x)
+    layer.values = np.full(c, 2.0 ** -20, np.float32)
+    layer.x = (2.0 ** rng.integers(-4, 11, layer.x.shape)).astype(np.float16)
+    note("half subnormal w")
+    assert np.array_equal(gpu_run(layer).astype(np.float64), layer.x.astype(np.float64) * 2.0 ** -20)
 
 
 @pytest.mark.parametrize("spec", [(70, 45, 8, 8, 5), (70, 45, 7, 7, 9), (70, 45, 1, 3, 30), (40, 96, 28, 28, 70),
@@ -154,6 +185,7 @@ def test_half_infinities_and_nans_stay_on_their_rows(hw, act):
     x[3, 69, -1, -1] = np.nan
     x[3, 12, 0, 0] = np.inf
     note("half non-finite %s %s" % (hw, act))
+    assert_runs(layer, "half")
     y = gpu_run(layer, x=x).astype(np.float64)
     wd = densify(45, 70, 1, layer.row_ptr, layer.col_idx, layer.values)
     stored = densify(45, 70, 1, layer.row_ptr, layer.col_idx, np.ones_like(layer.values)) > 0

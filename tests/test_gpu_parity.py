@@ -12,7 +12,7 @@ import pytest
 
 from synth import make_layer, expand_blocks_to_csr, config_layers
 from synth.configs import build
-from gpu_util import gpu_run, assert_parity, note, to_gpu, device
+from gpu_util import gpu_run, assert_parity, assert_runs, note, to_gpu, device
 
 pytestmark = pytest.mark.gpu
 
@@ -63,6 +63,23 @@ def test_small_shapes(spec):
     layer = make_layer(cin, cout, h, w, n, s, block_rows=k, storage=storage, act=act, seed=zlib.crc32(repr(spec).encode()) % 1000)
     note("small %s" % (spec,))
     assert_parity(layer, gpu_run(layer), what=str(spec))
+
+
+@pytest.mark.parametrize("kernel", [1, 2], ids=["strip", "direct"])
+@pytest.mark.parametrize("spec", SMALL, ids=lambda s: "%d-%d-%dx%d-n%d-s%g-k%d-%s-%s" % s)
+def test_small_shapes_on_the_strip_and_the_direct_kernel(spec, kernel):
+    """The same shapes where these kernels are asked for (the automatic choice
+    runs most of them on others); a strip that does not fit is refused."""
+    from paper_1911_09723_amd import SpconvError
+    cin, cout, h, w, n, s, k, storage, act = spec
+    layer = make_layer(cin, cout, h, w, n, s, block_rows=k, storage=storage, act=act, seed=zlib.crc32(repr(spec).encode()) % 1000)
+    note("small %s kernel %d" % (spec, kernel))
+    try:
+        y = gpu_run(layer, kernel=kernel)
+    except SpconvError as e:
+        assert kernel == 1 and e.status == 4 and cin > 600
+        return
+    assert_parity(layer, y, what=str(spec))
 
 
 def _workload_cases():
@@ -140,6 +157,7 @@ def test_single_nonzero_per_row_is_exact_fma():
 def test_run_is_deterministic_and_independent_of_planning():
     layer = make_layer(256, 256, 14, 14, 4, 0.85, act="relu", seed=9)
     note("determinism")
+    assert_runs(layer, "rows")
     base = gpu_run(layer)
     assert np.array_equal(base, gpu_run(layer))
     for opts in (dict(reorder=0), dict(group_lanes=8), dict(group_lanes=16), dict(kernel=2),
@@ -147,6 +165,7 @@ def test_run_is_deterministic_and_independent_of_planning():
                  dict(group_lanes=8, waves=16), dict(pipe_sets=1), dict(regions=1), dict(regions=3),
                  dict(pipe_sets=1, regions=2), dict(pipe_sets=2, waves=7)):
         note("determinism %s" % opts)
+        assert_runs(layer, "direct" if opts.get("kernel") == 2 else "strip", **opts)
         assert np.array_equal(base, gpu_run(layer, **opts)), opts
 
 
@@ -157,7 +176,9 @@ def test_shared_tail_tiles(n, k):
     rounds are split by bundles over several workgroups."""
     layer = make_layer(512, 512, 14, 14, n, 0.9, block_rows=k, act="relu", seed=11 + n)
     note("tail split n=%d k=%d" % (n, k))
-    assert_parity(layer, gpu_run(layer), what="tail n=%d k=%d" % (n, k))
+    y = gpu_run(layer, kernel=1)
+    assert_parity(layer, y, what="tail n=%d k=%d" % (n, k))
+    assert np.array_equal(y, gpu_run(layer))  # the automatic choice (row or lockstep kernel on some): the same bits
 
 
 @pytest.mark.parametrize("opts", [dict(), dict(pipe_sets=1), dict(regions=1), dict(regions=2),
@@ -169,6 +190,7 @@ def test_pipelined_rounds_bitwise_equal_simple_path(opts):
     same bits, and they match the oracle."""
     layer = make_layer(512, 512, 14, 14, 256, 0.9, act="relu", seed=21)
     note("pipelined rounds %s" % opts)
+    assert_runs(layer, "strip", **opts)
     y = gpu_run(layer, **opts)
     ref = gpu_run(layer, kernel=2)  # direct-load kernel: no strip, no pipeline
     assert np.array_equal(y, ref), opts
@@ -204,15 +226,16 @@ def test_batch_split_bitwise():
     assert np.array_equal(whole, np.concatenate(parts))
 
 
+@pytest.mark.parametrize("kernel", [0, 1, 2], ids=["auto", "strip", "direct"])
 @pytest.mark.parametrize("storage", ["f32", "f16"])
-def test_unaligned_pointers_take_scalar_path(storage):
+def test_unaligned_pointers_take_scalar_path(storage, kernel):
     """x and y offset by one element from 16-byte alignment give the same bits."""
     import torch
     from paper_1911_09723_amd import Plan
     layer = make_layer(64, 64, 8, 8, 2, 0.7, storage=storage, act="relu", seed=12)
-    note("unaligned %s" % storage)
-    ref = gpu_run(layer)
-    plan = Plan.from_layer(layer)
+    note("unaligned %s kernel %d" % (storage, kernel))
+    ref = gpu_run(layer, kernel=kernel)
+    plan = Plan.from_layer(layer, kernel=kernel)
     try:
         flat = to_gpu(np.concatenate([np.zeros(1, layer.x.dtype), layer.x.ravel()]))
         x = flat[1:].view(layer.x.shape)

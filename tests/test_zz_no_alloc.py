@@ -42,7 +42,7 @@ def test_static_plan_cannot_be_host_only():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("kernel", [0, 3])
+@pytest.mark.parametrize("kernel", [0, 1, 3])
 def test_static_plans_match_allocated_plans_twice_in_a_row(kernel):
     import torch
     from gpu_util import note, to_gpu, assert_parity
@@ -79,4 +79,31 @@ def test_static_plans_match_allocated_plans_twice_in_a_row(kernel):
         assert torch.all(y == 7.0)
     finally:
         for h in plans:
+            sp.spconv_destroy(h)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("cin,cout,s,storage,name", [(1200, 5400, 0.75, "f16", "half"), (512, 4096, 0.65, "f32", "outer")])
+def test_static_plans_too_large_with_the_newest_arrays_run_without_them(cin, cout, s, storage, name):
+    """The arrays of the half and of the row kernels are left out where the
+    image fits only without them: the plan is created, and an fp16 plan runs another kernel."""
+    import torch
+    from gpu_util import note, to_gpu, assert_parity
+    layer = make_layer(cin, cout, 7, 7, 1, s, storage=storage, act="relu", seed=63)
+    note("no-alloc large plan %d -> %d %s" % (cin, cout, storage))
+    args = (cout, cin, 1, layer.row_ptr, layer.col_idx, layer.values, layer.bias, layer.act, storage)
+    x = to_gpu(layer.x)
+    y = torch.empty((1, cout, 7, 7), device=x.device, dtype=x.dtype)
+    for create in (sp.spconv_plan_create, sp.spconv_plan_create_static):
+        h = create(*args)
+        try:
+            size, kernel = spmod.spconv_plan_get_info(h)["device_bytes"], sp.spconv_plan_run_kernel(h, 1, 7, 7)
+            if create is sp.spconv_plan_create:
+                assert size > sp.SPCONV_STATIC_PLAN_BYTES and kernel == name, (size, kernel)
+            else:
+                assert size <= sp.SPCONV_STATIC_PLAN_BYTES and kernel != "half", (size, kernel)
+            sp.spconv_run(h, x, y, 1, 7, 7)
+            torch.cuda.synchronize()
+            assert_parity(layer, y.cpu().numpy(), what="large plan")
+        finally:
             sp.spconv_destroy(h)
