@@ -222,7 +222,7 @@ constexpr int32_t kOuterMaxCin16 = 1264;
 // half 512 (t * hkb + b), and its lane l holds the 8 weights of row 16 t + l %
 // 16 at channels 32 b + 8 (l / 16) .. + 7.  Beside them the stored weights by
 // output channel (trow_ptr, tent: channel, fp32 bits), which the kernel sums
-// instead wherever it meets an infinity or a NaN, and the biases (tbias,
+// instead in the columns that hold an infinity or a NaN, and the biases (tbias,
 // padded to whole groups of 32 rows).
 constexpr int32_t kHalfMaxCin = 1216;               // 64 columns of X and their table fit in LDS
 constexpr int64_t kHalfMaxFragBytes = 16 << 20;     // dense weights kept beside the packed ones
@@ -232,7 +232,8 @@ constexpr int64_t kHalfMaxFragBytes = 16 << 20;     // dense weights kept beside
 // for the half kernel (the kernel for few columns walks them).  A row that the
 // strip plan packs as two pieces is summed as two here as well, its even and its
 // odd weights (the same bits; one chain of them all has 10% more rounding error
-// on heavy-tailed layers): kRowSplit marks it in trow_ptr, and in the streams
+// on heavy-tailed layers; not in plans too wide for a strip, whose long runs sum
+// rows in one chain): kRowSplit marks it in trow_ptr, and in the streams
 // below it is two entries, one after the other.  The LDS kernel
 // walks streams of groups of kGroupRecs stored weights: a row's weights in
 // ascending channel, the last group padded with weight 0 at channel cin (a row

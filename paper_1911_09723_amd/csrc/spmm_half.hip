@@ -4,7 +4,7 @@
 //
 // Why dense fragments.  A column costs (cin + cout) * 2 bytes of HBM traffic
 // and, multiplied out, cin * cout multiply-adds.  The fp16 16x16x32
-// instruction does 8192 of them in 7.6 ns per SIMD (1.1 P/s on the card), so
+// instruction does 8192 of them in 7.6 ns per SIMD (1.1e15 a second on the card), so
 // up to cin * cout / (cin + cout) = 360 even the dense product takes less
 // time than the traffic at 6.2 TB/s; walking only the stored 10% of the
 // weights costs an LDS read per 4 stored weights.
@@ -28,12 +28,13 @@
 // barrier each wavefront walks row tiles: per 32 input channels one weight
 // fragment (16 bytes a lane, from L2) and 4 operands a part from LDS.
 //
-// Measured (kernel time, batch 512, 90% 1 x 4 blocks; the lockstep kernel
-// before): 112 -> 672 @ 14 x 14 81 -> 46 us (floor 25 at 6.2 TB/s), 320 -> 1280
-// @ 7 x 7 81 -> 49, 192 -> 1152 @ 7 x 7 69 -> 34, 80 -> 480 @ 14 x 14 63 -> 31,
-// 40 -> 240 @ 28 x 28 112 -> 54.  What is left over the floor: staging, products
-// and stores of a workgroup follow each other, and a run has too few
-// workgroups per compute unit to hide all of one behind the others.
+// Measured (kernel time over back-to-back launches, batch 512, 90% 1 x 4 blocks; the
+// automatic choice before, the bytes at 6.2 TB/s): 112 -> 672 @ 14 x 14 82 -> 41 us
+// (25), 320 -> 1280 @ 7 x 7 78 -> 46 (13), 192 -> 1152 @ 7 x 7 66 -> 32 (11), 80 ->
+// 480 @ 14 x 14 63 -> 26 (18), 40 -> 240 @ 28 x 28 112 -> 54 (36).  What is left
+// over the bytes: staging, products and stores of a workgroup follow each other,
+// and a run has too few workgroups per compute unit to hide all of one behind the
+// others.
 //
 // A dense product reads X where the sparse one does not, and 0 * inf is NaN.
 // Staging therefore checks every value: a workgroup that saw an infinity or a
@@ -77,7 +78,7 @@ struct HArgs {
     const int32_t *row_ptr;  // stored weights by output channel (the non-finite path)
     const u2 *ent;           // channel, fp32 weight bits
     int32_t cin, cout, hw, images;
-    int32_t kb, rgroups;     // blocks of 32 input channels, groups of 32 output channels
+    int32_t kb, rgroups;     // blocks of 32 input channels, groups of RT row tiles (16 output channels each)
     int32_t units;           // 4-column units of a plane
     int32_t tunits, tiles;   // units of a tile; tiles
     int32_t ipt, tpi;        // images per tile (tpi = 1), or tiles per image (ipt = 1)
